@@ -60,6 +60,11 @@ typedef enum { MM_R32 = 0, MM_R64 = 1, MM_C64 = 2, MM_C128 = 3 } mm_dtype;
 /* Arithmetic of the contractions.
  *  MM_PREC_FP64         FP64 MFMA, FP64 state.
  *  MM_PREC_FP32         FP32 MFMA, FP32 state.
+ *                       Complex products of both run in three real products
+ *                       (square operators as L - I with the input added back)
+ *                       where that is as accurate: an entry of a fibre that
+ *                       holds Inf / NaN makes both components of the whole
+ *                       output fibre non-finite.
  *  MM_PREC_SPLIT_BF16X3 operator and state split into three RNE bfloat16
  *                       pieces each (x = x0 + x1 + x2); the six piece
  *                       products x_a y_b with a + b <= 2 run on BF16 MFMA with
@@ -361,11 +366,14 @@ mm_status mm_tune_save(mm_ctx ctx, const char* path);
 mm_status mm_tune_load(mm_ctx ctx, const char* path);
 
 /* Context options.
- *   MM_OPT_SMALL_RUN (default 1): mumode_expstep with nsteps >= 2, plain
- *     FP64 or FP32 operators, a state of at most 2 MiB and modes of at most
- *     128 real rows runs all steps in one single-workgroup launch (the
- *     launch latency otherwise dominates such problems); 0 uses one launch
- *     per product.
+ *   MM_OPT_SMALL_RUN (default 1): mumode_expstep with nsteps >= 2 and FP64 or
+ *     FP32 operators of at most 256 complex / 512 real rows runs several steps
+ *     of a mode in one launch, the fibres staying on chip between them
+ *     (products along different modes commute, so the modes' steps may be
+ *     reordered; blocks of steps keep intermediate growth within 2^20 in FP32,
+ *     2^200 in FP64, by the operators' norms); 2-D real FP64 states with both
+ *     modes at most 64 long run all steps in one single-workgroup launch.  0
+ *     uses one launch per product.
  *   MM_OPT_MONITOR_EVERY (default 0 = off): mumode_expstep and
  *     gpe_strang_step record the FP64 sum |T|^2 (the discrete mass without the
  *     cell volume, §2) after every `value` steps and after the last one, on

@@ -6,5 +6,4 @@ namespace mm {
 KernFn pick_kernel_f32_ida(int cplx, int ld, int pro, int epi, int cls, int full) {
   return pick_kernel<KP_F32, true>(cplx, ld, pro, epi, cls, full);
 }
-BatchFn pick_batch_merged_f32_ida() { return pick_batch_merged<KP_F32, true>(); }
 }  // namespace mm

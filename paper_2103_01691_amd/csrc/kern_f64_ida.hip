@@ -6,5 +6,4 @@ namespace mm {
 KernFn pick_kernel_f64_ida(int cplx, int ld, int pro, int epi, int cls, int full) {
   return pick_kernel<KP_F64, true>(cplx, ld, pro, epi, cls, full);
 }
-BatchFn pick_batch_merged_f64_ida() { return pick_batch_merged<KP_F64, true>(); }
 }  // namespace mm

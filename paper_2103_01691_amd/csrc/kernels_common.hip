@@ -98,6 +98,53 @@ __device__ __forceinline__ void prepare_slot(int64_t s, const double* __restrict
   }
 }
 
+// One lane slot s = (unit, fragment, lane) of the resident layout: 16 bytes of
+// operator entries, UK K-blocks of 4 columns ((re, im) pairs when complex).
+// Lane l holds row l % 16 of its 16-row fragment and column l / 16 of each
+// K-block; the FP64 accumulator keeps physical row l / 16 + 4 r in register r,
+// so its rows are permuted to give every lane four consecutive rows, as the
+// FP32 accumulator does.
+template <typename S>
+__device__ __forceinline__ void prepare_res_slot(int64_t s, const double* __restrict__ master, int64_t rows,
+                                                 int64_t cols, int64_t ld, int cplx, const PhaseScale& ph,
+                                                 void* __restrict__ outv, int KU, int MFT) {
+  if (s >= (int64_t)KU * MFT * 64) return;
+  const int lane = (int)(s % 64);
+  const int64_t t = s / 64;
+  const int mf = (int)(t % MFT);
+  const int64_t ku = t / MFT;
+  const int rho = lane % 16;
+  const int64_t i = (int64_t)mf * 16 + (sizeof(S) == 8 ? 4 * (rho % 4) + rho / 4 : rho);
+  const int comps = cplx ? 2 : 1;
+  const int UK = 16 / (int)(sizeof(S) * comps);
+  S* out = (S*)outv + s * (16 / sizeof(S));
+  for (int u = 0; u < UK; ++u) {
+    const int64_t j = (ku * UK + u) * 4 + lane / 16;
+    double re = 0.0, im = 0.0;
+    if (i < rows && j < cols) {
+      if (cplx) {
+        re = master[2 * (i + j * ld)];
+        im = master[2 * (i + j * ld) + 1];
+        double th = 0.0;
+        if (ph.rx2) th += ph.rc * ph.rx2[i];
+        if (ph.cx2) th += ph.cc * ph.cx2[j];
+        if (th != 0.0) {
+          double sn, cs;
+          sincos(th, &sn, &cs);
+          const double r2 = re * cs + im * sn;
+          im = im * cs - re * sn;
+          re = r2;
+        }
+      } else {
+        re = master[i + j * ld];
+      }
+    }
+    if (ph.minus_id && i == j && i < rows && j < cols) re -= 1.0;
+    out[u * comps] = (S)re;
+    if (cplx) out[u * comps + 1] = (S)im;
+  }
+}
+
 // Three-product (Gauss) preparation: slot ((jb * 3 + t) * MFT + mf, lane)
 // holds 8 columns of complex row mf * 32 + lane % 32 of Re L (t = 0), Im L
 // (t = 1) or Re L + Im L (t = 2), formed in FP64.
@@ -127,21 +174,22 @@ __global__ void prepare_gauss_kernel(const double* __restrict__ master, int64_t 
   }
 }
 
+// One slot of any operator layout (KPrec or KLayout code LY).
+template <int LY>
+__device__ __forceinline__ void prepare_any(int64_t s, const double* __restrict__ master, int64_t rows, int64_t cols,
+                                            int64_t ld, int cplx, const PhaseScale& ph, void* __restrict__ outv,
+                                            int KBT, int MFT, int a_exp) {
+  if constexpr (LY == KY_RES64) prepare_res_slot<double>(s, master, rows, cols, ld, cplx, ph, outv, KBT, MFT);
+  else if constexpr (LY == KY_RES32) prepare_res_slot<float>(s, master, rows, cols, ld, cplx, ph, outv, KBT, MFT);
+  else prepare_slot<LY>(s, master, rows, cols, ld, cplx, ph, outv, KBT, MFT, a_exp);
+}
+
 template <int PR>
 __global__ void prepare_kernel(const double* __restrict__ master, int64_t rows, int64_t cols,
                                int64_t ld, int cplx, PhaseScale ph, void* __restrict__ outv, int KBT,
                                int MFT, int a_exp) {
-  prepare_slot<PR>((int64_t)blockIdx.x * blockDim.x + threadIdx.x, master, rows, cols, ld, cplx, ph, outv, KBT,
-                   MFT, a_exp);
-}
-
-// Several operators of one precision in one launch (blockIdx.y selects the
-// operator): the per-step operators of a time-dependent splitting step.
-template <int PR>
-__global__ void prepare_multi_kernel(PrepJobs jobs) {
-  const PrepJob& p = jobs.j[blockIdx.y];
-  prepare_slot<PR>((int64_t)blockIdx.x * blockDim.x + threadIdx.x, p.master, p.rows, p.cols, p.ld, p.cplx, p.ph,
-                   p.out, p.KBT, p.MFT, p.a_exp);
+  prepare_any<PR>((int64_t)blockIdx.x * blockDim.x + threadIdx.x, master, rows, cols, ld, cplx, ph, outv, KBT,
+                  MFT, a_exp);
 }
 
 // Per-step operators of the time-dependent harmonic-oscillator splitting
@@ -158,8 +206,8 @@ __global__ void prepare_steps_kernel(StepPrep p) {
   ph.cx2 = m.x2;
   ph.cc = 0.5 * p.eps * (cos(t) - cos(th));           // first half step: columns
   ph.rc = 0.5 * p.eps * (cos(th) - cos(t + p.tau));   // second half step: rows
-  prepare_slot<PR>((int64_t)blockIdx.x * blockDim.x + threadIdx.x, m.master, m.n, m.n, m.n, 1, ph,
-                   m.out + (size_t)st * m.stride, m.KBT, m.MFT, m.a_exp);
+  prepare_any<PR>((int64_t)blockIdx.x * blockDim.x + threadIdx.x, m.master, m.n, m.n, m.n, 1, ph,
+                  m.out + (size_t)st * m.stride, m.KBT, m.MFT, m.a_exp);
 }
 
 // ------------------------------------------------------------- norm2 ------
@@ -450,7 +498,16 @@ void op_blocks(int prec, int64_t Mr, int64_t Kr, int* KBT, int* MFT) {
   *MFT = (int)((mf + g.MPAD - 1) / g.MPAD * g.MPAD);
 }
 
+void res_blocks(int lay, int64_t rows, int64_t cols, int cplx, int* KU, int* MFT) {
+  const int uk = 16 / ((lay == KY_RES64 ? 8 : 4) * (cplx ? 2 : 1));
+  // padding that no wave of at most 4 fragments and no ring of 4 units (from
+  // any unit of the last chunk) reads past
+  *KU = (int)(((cols + 3) / 4 + uk - 1) / uk) + 4;
+  *MFT = (int)((rows + 15) / 16) + 3;
+}
+
 size_t prepared_bytes(int prec, int KBT, int MFT) {
+  if (prec == KY_RES64 || prec == KY_RES32) return (size_t)KBT * MFT * 64 * 16;
   FragGeom g = frag_geom(prec);
   size_t elems = (size_t)KBT * MFT * g.NPC * 64 * g.KPL;
   size_t es = prec == KP_F64 ? 8 : prec == KP_F32 ? 4 : 2;
@@ -458,7 +515,52 @@ size_t prepared_bytes(int prec, int KBT, int MFT) {
 }
 
 int num_classes(int prec) {
-  return (prec == KP_BF16X3 || prec == KP_FP16X2) ? 11 : (prec == KP_F64 ? 4 : 3);
+  return (prec == KP_BF16X3 || prec == KP_FP16X2) ? 11 : ((prec == KP_F64 || prec == KP_F32) ? 4 : 3);
+}
+
+// Fragments per wave (MF) by the operator's rows: one up to 64 rows (four
+// waves already share the tile), two up to 256 (at most eight waves, 128
+// registers or fewer, so four waves fit each SIMD), four above (real
+// operators of up to 512 rows).  Short operators put several 16-fibre groups
+// in one workgroup, unless that would leave fewer than two workgroups per CU.
+void res_plan(int prec, int form, bool ph, int cls, bool split_rows, ResArgs* a, ResPlan* p) {
+  const int frags = (a->m + 15) / 16;
+  int mf = cls >= 0 ? std::min(cls, 3) + 1
+                    : (frags <= 4 ? 1 : (frags <= 8 ? 2 : (frags <= 12 ? 3 : (frags <= 16 ? 2 : 4))));
+  if (split_rows) mf = 1;
+  while (mf < 4 && (frags + mf - 1) / mf > (mf == 1 ? 16 : 8)) ++mf;
+  p->prec = prec;
+  p->form = form;
+  p->mf = mf;
+  p->ph = ph ? 1 : 0;
+  a->WM = split_rows ? 1 : (frags + mf - 1) / mf;
+  a->WN = split_rows ? 1 : (a->WM == 1 ? 4 : (a->WM == 2 ? 2 : 1));
+  p->nf = (form == RF_RR && a->n <= 256 && a->F >= 16384) ? 2 : 1;
+  while (a->WN > 1 && (a->F + 16 * p->nf * a->WN - 1) / (16 * p->nf * a->WN) < 512) a->WN /= 2;
+  a->NRB = 1;
+  const int nt = 16 * p->nf * a->WN;
+  const int es = (prec == KP_F64 ? 8 : 4) * (form == RF_RR ? 1 : 2);
+  p->threads = 64 * a->WM * a->WN;
+  p->grid_x = (int)((a->F + nt - 1) / nt);
+  p->grid_y = split_rows ? frags : 1;
+  p->lds = (size_t)res_lds_rows(a->n) * (nt + 1) * es;
+}
+
+// Four waves for every item of a batch: WM of them along the rows.
+void res_batch_plan(int prec, int form, ResArgs* a, int* kind, int64_t* tiles, size_t* lds) {
+  const int frags = (a->m + 15) / 16;
+  a->WM = frags <= 1 ? 1 : (frags <= 2 ? 2 : 4);
+  a->WN = 4 / a->WM;
+  a->NRB = (frags + 15) / 16;
+  const int mf = (frags + a->WM * a->NRB - 1) / (a->WM * a->NRB);
+  *kind = form * 10 + mf;
+  const int nt = 16 * a->WN;
+  *tiles = (a->F + nt - 1) / nt;
+  *lds = (size_t)res_lds_rows(a->n) * (nt + 1) * (prec == KP_F64 ? 8 : 4) * (form == RF_RR ? 1 : 2);
+}
+
+hipError_t launch_res(const ResPlan& p, const ResArgs& a, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
+  return p.prec == KP_F64 ? launch_res_f64(p, a, s, start, stop) : launch_res_f32(p, a, s, start, stop);
 }
 
 void gauss_blocks(int64_t rows, int64_t cols, int* JBT, int* MFT) {
@@ -562,30 +664,12 @@ hipError_t launch_mode(const ModePlan& p, const ModeArgs& a, hipStream_t s, hipE
 hipError_t launch_mode_batch_merged(int prec, int ida, const BatchItem* items, int count, hipStream_t s) {
   BatchFn fn = nullptr;
   switch (prec) {
-    case KP_F64: fn = ida ? pick_batch_merged_f64_ida() : pick_batch_merged_f64(); break;
-    case KP_F32: fn = ida ? pick_batch_merged_f32_ida() : pick_batch_merged_f32(); break;
     case KP_BF16X3: fn = ida ? pick_batch_merged_bf16x3_ida() : pick_batch_merged_bf16x3(); break;
     case KP_BF16: fn = ida ? pick_batch_merged_bf16_ida() : pick_batch_merged_bf16(); break;
     default: return hipErrorInvalidDeviceFunction;
   }
   if (count <= 0) return hipSuccess;
   hipLaunchKernelGGL(fn, dim3(count), dim3(256), 0, s, items);
-  return hipGetLastError();
-}
-
-hipError_t launch_prepare_multi(int prec, const PrepJobs& jobs, hipStream_t s) {
-  if (jobs.n < 1 || jobs.n > MAX_PREP_JOBS) return hipErrorInvalidValue;
-  int64_t slots = 0;
-  for (int k = 0; k < jobs.n; ++k) slots = std::max(slots, (int64_t)jobs.j[k].KBT * jobs.j[k].MFT * 64);
-  const int threads = 256;
-  const dim3 grid((unsigned)((slots + threads - 1) / threads), (unsigned)jobs.n);
-  switch (prec) {
-    case KP_F64: hipLaunchKernelGGL(prepare_multi_kernel<KP_F64>, grid, dim3(threads), 0, s, jobs); break;
-    case KP_F32: hipLaunchKernelGGL(prepare_multi_kernel<KP_F32>, grid, dim3(threads), 0, s, jobs); break;
-    case KP_BF16X3: hipLaunchKernelGGL(prepare_multi_kernel<KP_BF16X3>, grid, dim3(threads), 0, s, jobs); break;
-    case KP_FP16X2: hipLaunchKernelGGL(prepare_multi_kernel<KP_FP16X2>, grid, dim3(threads), 0, s, jobs); break;
-    default: hipLaunchKernelGGL(prepare_multi_kernel<KP_BF16>, grid, dim3(threads), 0, s, jobs); break;
-  }
   return hipGetLastError();
 }
 
@@ -599,6 +683,8 @@ hipError_t launch_prepare_steps(int prec, const StepPrep& p, hipStream_t s) {
     case KP_F32: hipLaunchKernelGGL(prepare_steps_kernel<KP_F32>, grid, dim3(256), 0, s, p); break;
     case KP_BF16X3: hipLaunchKernelGGL(prepare_steps_kernel<KP_BF16X3>, grid, dim3(256), 0, s, p); break;
     case KP_FP16X2: hipLaunchKernelGGL(prepare_steps_kernel<KP_FP16X2>, grid, dim3(256), 0, s, p); break;
+    case KY_RES64: hipLaunchKernelGGL(prepare_steps_kernel<KY_RES64>, grid, dim3(256), 0, s, p); break;
+    case KY_RES32: hipLaunchKernelGGL(prepare_steps_kernel<KY_RES32>, grid, dim3(256), 0, s, p); break;
     default: hipLaunchKernelGGL(prepare_steps_kernel<KP_BF16>, grid, dim3(256), 0, s, p); break;
   }
   return hipGetLastError();
@@ -622,6 +708,14 @@ hipError_t launch_prepare(int prec, int cplx, const double* master, int64_t rows
     case KP_BF16X3:
       hipLaunchKernelGGL(prepare_kernel<KP_BF16X3>, dim3(blocks), dim3(threads), 0, s, master,
                          rows, cols, ld, cplx, ph, out, KBT, MFT, a_exp);
+      break;
+    case KY_RES64:
+      hipLaunchKernelGGL(prepare_kernel<KY_RES64>, dim3(blocks), dim3(threads), 0, s, master, rows,
+                         cols, ld, cplx, ph, out, KBT, MFT, a_exp);
+      break;
+    case KY_RES32:
+      hipLaunchKernelGGL(prepare_kernel<KY_RES32>, dim3(blocks), dim3(threads), 0, s, master, rows,
+                         cols, ld, cplx, ph, out, KBT, MFT, a_exp);
       break;
     case KP_FP16X2:
       hipLaunchKernelGGL(prepare_kernel<KP_FP16X2>, dim3(blocks), dim3(threads), 0, s, master,

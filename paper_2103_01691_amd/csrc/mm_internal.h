@@ -7,6 +7,11 @@
 namespace mm {
 
 enum KPrec { KP_F64 = 0, KP_F32 = 1, KP_BF16X3 = 2, KP_FP16X2 = 3, KP_BF16 = 4 };
+// Operator layouts: the precision codes above name the fragment order of the
+// chunked kernels (mode_tile.h); these two are the layouts of the resident-
+// tile kernels (resident.h).  KBT counts 16-byte units along K, MFT 16-row
+// fragments.
+enum KLayout { KY_RES64 = 5, KY_RES32 = 6 };
 // Fibre load paths: KCONTIG fibres contiguous (mu = 1, P = 1); FCONTIG
 // fibres interleaved with P % 4 == 0 (16-byte loads along P); GENERIC any
 // P (gather); PAIR P == 2, pairs of fibres interleaved (a real operator on
@@ -27,6 +32,8 @@ FragGeom frag_geom(int prec);
 // Padded K-block and M-fragment counts of a prepared operator with Mr real
 // rows and Kr real columns.
 void op_blocks(int prec, int64_t Mr, int64_t Kr, int* KBT, int* MFT);
+// 16-byte units along K and 16-row fragments of a resident-layout operator.
+void res_blocks(int lay, int64_t rows, int64_t cols, int cplx, int* KU, int* MFT);
 
 // Arguments of one mu-mode product launch (real-GEMM view, see
 // mode_kernels.hip).  Complex tensors: P, Q, n, m count complex entries.
@@ -116,16 +123,66 @@ hipError_t launch_prepare_gauss(int prec, const double* master, int64_t rows, in
 // Merged batched launch: one kernel per precision runs work items of every
 // kind (complex / real, contiguous / strided fibres, tile class 0..2; all
 // 256 threads), so every instance tile of one mode goes in a single launch.
-BatchFn pick_batch_merged_f64();
-BatchFn pick_batch_merged_f32();
 BatchFn pick_batch_merged_bf16x3();
 BatchFn pick_batch_merged_bf16();
-BatchFn pick_batch_merged_f64_ida();
-BatchFn pick_batch_merged_f32_ida();
 BatchFn pick_batch_merged_bf16x3_ida();
 BatchFn pick_batch_merged_bf16_ida();
 // ida: the items' operators carry the identity split (a.idadd set on all)
 hipError_t launch_mode_batch_merged(int prec, int ida, const BatchItem* items, int count, hipStream_t s);
+
+// Resident-tile kernels (kern_res_<prec>.hip), FP64 and FP32: one launch
+// applies an operator of at most 256 complex / 512 real rows and columns to
+// every fibre, with the whole fibre tile in LDS (resident.h).
+// operator x state: complex x complex in three or four real products, real x
+// complex, real x real
+enum ResForm { RF_C3 = 0, RF_RC = 1, RF_RR = 2, RF_C4 = 3 };
+struct ResArgs {
+  const void* in;
+  void* out;
+  const void* A;         // operator in the KY_RES layout of its precision
+  int64_t P, F;          // fibre (p, q), q = f / P: entry j at p + P * (j + n * q)
+  int n, m;              // entries of an input / output fibre
+  int MFT;               // 16-row fragments of the prepared operator (padded)
+  int WM, WN;            // waves along rows and fibres
+  int NRB;               // row blocks a workgroup works through (1 when nsteps > 1)
+  int nsteps;            // products applied to the resident tile (square operators; 1 otherwise)
+  int idadd;             // the operator holds L - I: add the input back
+  double s_pre, s_post;  // phase coefficients (0: none)
+  // position-dependent phase exp((i s/2)(1 - W^-1 |v|^2)) instead of the
+  // Gross-Pitaevskii one: W^-1 = prod_j winv[j * 4096 + i_j] over the wd modes
+  // of lengths wdims; wmu is the (0-based) mode of this product
+  const double* winv;
+  int wd, wmu;
+  int64_t wdims[6];
+};
+// Longest operator side of the resident kernels.
+inline bool res_fits(int64_t rows, int64_t cols, int cplx) {
+  const int64_t lim = cplx ? 256 : 512;
+  return rows <= lim && cols <= lim;
+}
+// LDS rows of a tile: whole operator units and one K-block that is read ahead.
+inline int res_lds_rows(int n) { return (n + 15) / 16 * 16 + 4; }
+struct ResPlan {
+  int prec, form, mf, nf, ph, threads, grid_x, grid_y;
+  size_t lds;
+};
+// Launch shape of one product (fills a.WM / a.WN).  cls: tile class chosen by
+// the tuner (MF = cls + 1 fragments per wave), -1 for the built-in rule;
+// split_rows: out of place, rows may be spread over workgroups.
+void res_plan(int prec, int form, bool ph, int cls, bool split_rows, ResArgs* a, ResPlan* p);
+hipError_t launch_res(const ResPlan& p, const ResArgs& a, hipStream_t s, hipEvent_t start = nullptr,
+                      hipEvent_t stop = nullptr);
+hipError_t launch_res_f64(const ResPlan& p, const ResArgs& a, hipStream_t s, hipEvent_t start, hipEvent_t stop);
+hipError_t launch_res_f32(const ResPlan& p, const ResArgs& a, hipStream_t s, hipEvent_t start, hipEvent_t stop);
+// Batched form: work item i runs tile `tile` of args[arg] with the tile code
+// kind = form * 10 + MF (4 waves, NF = 1); res_batch_plan fills WM, WN, NRB.
+void res_batch_plan(int prec, int form, ResArgs* a, int* kind, int64_t* tiles, size_t* lds);
+struct ResItem {
+  int arg, kind;
+  int64_t tile;
+};
+hipError_t launch_res_batch_f64(const ResArgs* args, const ResItem* items, int count, size_t lds, hipStream_t s);
+hipError_t launch_res_batch_f32(const ResArgs* args, const ResItem* items, int count, size_t lds, hipStream_t s);
 
 // Per-launch plan chosen by the runtime.
 struct ModePlan {
@@ -137,6 +194,8 @@ struct ModePlan {
   bool covers_all_rows;
   int full;            // every tile complete and output offsets fit 32 bits
   int gauss;           // three-product kernel: the operator's Gauss preparation
+  int res = 0;         // resident-tile kernel (FP64 / FP32; rp is its launch shape)
+  ResPlan rp;
 };
 
 // Fill `plan` for the given problem; returns false if no kernel fits.
@@ -151,18 +210,6 @@ int num_classes(int prec);
 // start / stop (optional): events recorded by the launch itself
 hipError_t launch_mode(const ModePlan& plan, const ModeArgs& a, hipStream_t s, hipEvent_t start = nullptr,
                        hipEvent_t stop = nullptr);
-// Whole-run kernel for small states (kern_small.hip): one workgroup, every
-// step and mode of an expstep.  m[k].A == nullptr skips mode k; every mode
-// must be planned with tile class SMALL_RUN_CLASS covering all its rows, with
-// in == out == the state.
-#define SMALL_RUN_CLASS 2
-struct SmallRun {
-  ModeArgs m[6];
-  int load[6];
-  int tiles[6];   // fibre tiles of mode k (its plan's grid_x)
-  int d, nsteps;
-};
-hipError_t launch_small_run(int prec, int cplx, const SmallRun& r, int* threads_out, hipStream_t s);
 // Whole run of a 2-D real FP64 integrator (n1, n2 <= 64) in one workgroup
 // with the state and the operators resident in LDS (kern_small.hip): U
 // (n1 x n2, column-major) <- E1 U E2^T nsteps times; E1 / E2 are FP64
@@ -178,24 +225,8 @@ struct PhaseScale {
   double rc = 0.0;
   const double* cx2 = nullptr;
   double cc = 0.0;
+  int minus_id = 0;   // resident layouts: prepare L - I (products add the input back)
 };
-
-// One operator preparation (the arguments of launch_prepare).
-struct PrepJob {
-  const double* master = nullptr;
-  int64_t rows = 0, cols = 0, ld = 0;
-  int cplx = 0;
-  PhaseScale ph;
-  void* out = nullptr;
-  int KBT = 0, MFT = 0, a_exp = 0;
-};
-constexpr int MAX_PREP_JOBS = 6;
-struct PrepJobs {
-  PrepJob j[MAX_PREP_JOBS];
-  int n = 0;
-};
-// Up to MAX_PREP_JOBS preparations of one precision in one launch.
-hipError_t launch_prepare_multi(int prec, const PrepJobs& jobs, hipStream_t s);
 
 // The collapsed harmonic-oscillator propagators of `steps` consecutive steps
 // of the time-dependent splitting, for up to 6 modes of one precision, in

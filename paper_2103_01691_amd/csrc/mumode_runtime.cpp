@@ -29,10 +29,14 @@ struct mm_op_s {
   int64_t rows = 0, cols = 0;
   int cplx = 0;
   mm_prec prec = MM_PREC_FP64;
+  int lay = 0;                   // layout of prep: mm::KPrec or mm::KLayout code
   double* dev_master = nullptr;  // FP64 master on the device, ld = rows
   void* prep = nullptr;          // fragment-order operator (own complexity)
   int KBT = 0, MFT = 0;
   int a_exp = 0;                 // FP16X2: the pieces represent L * 2^-a_exp
+  double log2_norm = 0.0;        // log2 of a bound of ||L||_2, sqrt(||L||_1 ||L||_inf)
+  int res_id = 0;                // resident layout: prep holds L - I though the master does not
+  int res_c4 = 0;                // resident layout: four-product form
   int idsplit = 0;               // the master and pieces hold L - I; products add the input back
   void* prep_c = nullptr;        // real master promoted to complex (lazily)
   int KBT_c = 0, MFT_c = 0;
@@ -115,9 +119,12 @@ struct mm_ctx_s {
   std::vector<double> winv_w[MM_MAXD];
   // batched integrator: work items of the last batch signature, its
   // launch groups and the captured per-step graph
-  struct BatchGroup { mm::ModePlan plan; int ida, offset, count; };
+  struct BatchGroup { mm::ModePlan plan; int ida, offset, count; size_t lds; };
   mm::BatchItem* bitems = nullptr;
   size_t bitems_cap = 0;
+  mm::ResArgs* rargs = nullptr;   // resident-tile products of the batch and their tiles
+  mm::ResItem* ritems = nullptr;
+  size_t rargs_cap = 0, ritems_cap = 0;
   std::vector<BatchGroup> bgroups;
   std::vector<uint64_t> bsig;
   hipGraph_t bgraph = nullptr;
@@ -182,6 +189,21 @@ int kprec(mm_prec p) {
     case MM_PREC_SPLIT_FP16X2: return mm::KP_FP16X2;
     default: return mm::KP_BF16;
   }
+}
+
+// Layout an operator of this shape is prepared in: the resident-tile kernels'
+// for FP64 and FP32 up to their longest side, else the precision's own.
+int op_layout(mm_prec p, int64_t rows, int64_t cols, int cplx) {
+  if (mm::res_fits(rows, cols, cplx)) {
+    if (p == MM_PREC_FP64) return mm::KY_RES64;
+    if (p == MM_PREC_FP32) return mm::KY_RES32;
+  }
+  return kprec(p);
+}
+bool is_res(int lay) { return lay == mm::KY_RES64 || lay == mm::KY_RES32; }
+void layout_blocks(int lay, int64_t rows, int64_t cols, int cplx, int* KBT, int* MFT) {
+  if (is_res(lay)) mm::res_blocks(lay, rows, cols, cplx, KBT, MFT);
+  else mm::op_blocks(lay, (cplx ? 2 : 1) * rows, (cplx ? 2 : 1) * cols, KBT, MFT);
 }
 
 bool is_complex(mm_dtype t) { return t == MM_C64 || t == MM_C128; }
@@ -255,13 +277,55 @@ mm_status ensure_prepared(mm_ctx ctx, mm_op L, bool cplx, hipStream_t s, void** 
   return MM_OK;
 }
 
+// Launch through `fn(start, stop)`, with events stamped by the dispatch and a
+// record of `kind` while profiling.
+template <typename F>
+mm_status timed_launch(mm_ctx ctx, int kind, F&& fn) {
+  hipEvent_t e0 = nullptr, e1 = nullptr;
+  if (ctx->profiling) {
+    HIPCHK(ctx, hipEventCreate(&e0));
+    HIPCHK(ctx, hipEventCreate(&e1));
+  }
+  HIPCHK(ctx, fn(e0, e1));
+  if (ctx->profiling) ctx->recs.push_back({kind, e0, e1});
+  return MM_OK;
+}
+
+mm::ResForm res_form(const mm_op_s* L, mm_dtype dt) {
+  return L->cplx ? (L->res_c4 ? mm::RF_C4 : mm::RF_C3) : (is_complex(dt) ? mm::RF_RC : mm::RF_RR);
+}
+
+// Arguments of a resident-tile product (launch shape still open).
+mm::ResArgs res_args(const void* in, void* out, const int64_t* dims, int d, mm_dtype dt, const mm_op_s* L, int mu,
+                     double s_pre, double s_post) {
+  mm::ResArgs r = {};
+  int64_t P = 1, Q = 1;
+  for (int k = 0; k < mu - 1; ++k) P *= dims[k];
+  for (int k = mu; k < d; ++k) Q *= dims[k];
+  r.in = in;
+  r.out = out;
+  r.A = L->prep;
+  r.P = P;
+  r.F = P * Q;
+  r.n = (int)dims[mu - 1];
+  r.m = (int)L->rows;
+  r.MFT = L->MFT;
+  r.nsteps = 1;
+  r.idadd = (L->idsplit || L->res_id) ? 1 : 0;
+  if (is_complex(dt)) {
+    r.s_pre = s_pre;
+    r.s_post = s_post;
+  }
+  return r;
+}
+
 // One mode product out = in x_mu L on a tensor with dims `dims` (input dims),
 // optional fused phases.  `in` and `out` may be equal when the plan covers
 // all rows in one workgroup (checked by the caller through *in_place_ok).
 mm_status run_mode(mm_ctx ctx, const void* in, void* out, const int64_t* dims, int d, mm_dtype dt,
                    mm_op L, int mu, double s_pre, double s_post, hipStream_t s, mm::ModePlan* plan_out,
                    bool dry, const void* prep_override = nullptr, bool batch = false,
-                   mm::ModeArgs* args_out = nullptr) {
+                   bool split_rows = false, int nsteps = 1) {
   // A real operator on a complex state (with no fused phase) acts on the
   // (re, im) planes separately: the state is then the real tensor
   // (2, n_1, ..., n_d) and mode mu its mode mu + 1, i.e. two real fibres per
@@ -309,9 +373,33 @@ mm_status run_mode(mm_ctx ctx, const void* in, void* out, const int64_t* dims, i
     }
     if (it != ctx->tune.end()) force = it->second.first;
   }
+  if (is_res(L->lay)) {
+    // resident-tile kernel: the complex entries themselves are the fibres'
+    // entries (no real view), any P
+    mm::ResArgs r = res_args(in, out, dims, d, dt, L, mu, s_pre, s_post);
+    if (prep_override) r.A = prep_override;
+    r.nsteps = nsteps;
+    mm::ModePlan plan = {};
+    plan.prec = kprec(L->prec);
+    plan.cplx = cplx ? 1 : 0;
+    plan.load = load;
+    plan.pro = (cplx && s_pre != 0.0) ? 1 : 0;
+    plan.epi = (cplx && s_post != 0.0) ? 1 : 0;
+    plan.covers_all_rows = !split_rows;
+    plan.res = 1;
+    mm::res_plan(plan.prec, res_form(L, dt), plan.pro || plan.epi, force, split_rows, &r, &plan.rp);
+    plan.cls = force >= 0 ? std::min(force, 3) : plan.rp.mf - 1;
+    plan.grid_x = plan.rp.grid_x;
+    plan.grid_y = plan.rp.grid_y;
+    plan.threads = plan.rp.threads;
+    if (plan_out) *plan_out = plan;
+    if (dry) return MM_OK;
+    const int kind = plan.prec * 1000 + plan.cplx * 100 + plan.load * 10 + plan.pro * 2 + plan.epi;
+    return timed_launch(ctx, kind, [&](hipEvent_t e0, hipEvent_t e1) { return mm::launch_res(plan.rp, r, s, e0, e1); });
+  }
   // three-product kernels: complex operator with its Gauss preparation,
   // single-tensor products, whole staging tiles of 8 entries
-  const bool gauss_ok = L->prep_g && cplx && !batch && !prep_override && !args_out && a.n % 8 == 0;
+  const bool gauss_ok = L->prep_g && cplx && !batch && !prep_override && a.n % 8 == 0;
   mm::ModePlan plan;
   if (!mm::plan_mode(a, kprec(L->prec), cplx ? 1 : 0, s_pre != 0.0, s_post != 0.0, fcontig, kcontig, &plan, batch,
                      force, gauss_ok))
@@ -343,7 +431,6 @@ mm_status run_mode(mm_ctx ctx, const void* in, void* out, const int64_t* dims, i
     mm::op_blocks(kprec(L->prec), a.Mr, a.Kr, &a.KBT, &a.MFT);
   }
   if (plan_out) *plan_out = plan;
-  if (args_out) *args_out = a;
   if (dry) return MM_OK;
   if (plan.prec == mm::KP_FP16X2) {
     if (in != ctx->chain_end) {
@@ -358,17 +445,8 @@ mm_status run_mode(mm_ctx ctx, const void* in, void* out, const int64_t* dims, i
     ctx->sidx = (ctx->sidx + 1) % 3;
     ctx->chain_end = out;
   }
-  if (ctx->profiling) {
-    hipEvent_t e0, e1;
-    HIPCHK(ctx, hipEventCreate(&e0));
-    HIPCHK(ctx, hipEventCreate(&e1));
-    HIPCHK(ctx, mm::launch_mode(plan, a, s, e0, e1));
-    const int kind = plan.prec * 1000 + plan.cplx * 100 + plan.load * 10 + plan.pro * 2 + plan.epi;
-    ctx->recs.push_back({kind, e0, e1});
-    return MM_OK;
-  }
-  HIPCHK(ctx, mm::launch_mode(plan, a, s));
-  return MM_OK;
+  const int kind = plan.prec * 1000 + plan.cplx * 100 + plan.load * 10 + plan.pro * 2 + plan.epi;
+  return timed_launch(ctx, kind, [&](hipEvent_t e0, hipEvent_t e1) { return mm::launch_mode(plan, a, s, e0, e1); });
 }
 
 mm_status ensure_ws(mm_ctx ctx, size_t bytes) {
@@ -384,6 +462,30 @@ mm_status ensure_ws(mm_ctx ctx, size_t bytes) {
   if (hipMalloc(&ctx->ws, bytes) != hipSuccess) return fail(ctx, MM_ERR_NOMEM, "workspace of %zu bytes", bytes);
   ctx->ws_bytes = bytes;
   return MM_OK;
+}
+
+// Host array into a device buffer owned by the context, grown as needed.
+template <typename V>
+mm_status upload(mm_ctx ctx, V** dev, size_t* cap, const std::vector<V>& host) {
+  if (host.size() > *cap) {
+    if (*dev) {
+      HIPCHK(ctx, hipDeviceSynchronize());
+      HIPCHK(ctx, hipFree(*dev));
+      *dev = nullptr;
+      *cap = 0;
+    }
+    if (hipMalloc((void**)dev, host.size() * sizeof(V)) != hipSuccess)
+      return fail(ctx, MM_ERR_NOMEM, "batch work items");
+    *cap = host.size();
+  }
+  if (!host.empty()) HIPCHK(ctx, hipMemcpy(*dev, host.data(), host.size() * sizeof(V), hipMemcpyHostToDevice));
+  return MM_OK;
+}
+
+// Relative MFMA time of one batched tile.
+int64_t res_tile_cost(const mm::ResArgs& a, int kind) {
+  const int form = kind / 10, mf = kind % 10;
+  return (int64_t)a.n * mf * a.NRB * (form == mm::RF_C4 ? 4 : (form == mm::RF_C3 ? 3 : (form == mm::RF_RC ? 2 : 1)));
 }
 
 // Drop the captured batch graph and its signature: its work items hold
@@ -457,7 +559,8 @@ mm_op_s scratch_op(int n, mm_prec prec, int a_exp) {
   o.cplx = 1;
   o.prec = prec;
   o.a_exp = a_exp;
-  mm::op_blocks(kprec(prec), 2 * (int64_t)n, 2 * (int64_t)n, &o.KBT, &o.MFT);
+  o.lay = op_layout(prec, n, n, 1);
+  layout_blocks(o.lay, n, n, 1, &o.KBT, &o.MFT);
   return o;
 }
 
@@ -476,7 +579,7 @@ mm_status expm_device(mm_ctx ctx, int n, const double* A, const double* d, doubl
   mm_status st = grow(ctx, (void**)&ctx->ex_buf, &ctx->ex_bytes, sizeof(double) * (6 * mat + n));
   if (st != MM_OK) return st;
   mm_op_s op = scratch_op(n, MM_PREC_FP64, 0);
-  const size_t pb = mm::prepared_bytes(mm::KP_F64, op.KBT, op.MFT);
+  const size_t pb = mm::prepared_bytes(op.lay, op.KBT, op.MFT);
   st = grow(ctx, &ctx->ex_prep, &ctx->ex_prep_bytes, 2 * pb);
   if (st != MM_OK) return st;
   double* X = ctx->ex_buf;
@@ -510,16 +613,16 @@ mm_status expm_device(mm_ctx ctx, int n, const double* A, const double* d, doubl
   auto mul = [&](const void* prep, const double* in, double* o) {
     const int keep = ctx->force_cls;
     if (few) ctx->force_cls = 3;
-    mm_status r = run_mode(ctx, in, o, dims, 2, MM_C128, &op, 1, 0, 0, s, nullptr, false, prep);
+    mm_status r = run_mode(ctx, in, o, dims, 2, MM_C128, &op, 1, 0, 0, s, nullptr, false, prep, false, is_res(op.lay));
     ctx->force_cls = keep;
     return r;
   };
   HIPCHK(ctx, mm::launch_expm_generator(A, n, d, gr, gi, fr * sc, fi * sc, X, s));
-  HIPCHK(ctx, mm::launch_prepare(mm::KP_F64, 1, X, n, n, n, mm::PhaseScale(), prepX, op.KBT, op.MFT, s));
+  HIPCHK(ctx, mm::launch_prepare(op.lay, 1, X, n, n, n, mm::PhaseScale(), prepX, op.KBT, op.MFT, s));
   if ((st = mul(prepX, X, X2)) != MM_OK) return st;
   if ((st = mul(prepX, X2, X3)) != MM_OK) return st;
   if ((st = mul(prepX, X3, Y)) != MM_OK) return st;
-  HIPCHK(ctx, mm::launch_prepare(mm::KP_F64, 1, Y, n, n, n, mm::PhaseScale(), prepY, op.KBT, op.MFT, s));
+  HIPCHK(ctx, mm::launch_prepare(op.lay, 1, Y, n, n, n, mm::PhaseScale(), prepY, op.KBT, op.MFT, s));
   // coefficients 1/k!, k = 0..18, in blocks B_j = sum_i c_{4j+i} X^i
   double c[20] = {0};
   c[0] = 1.0;
@@ -531,7 +634,7 @@ mm_status expm_device(mm_ctx ctx, int n, const double* A, const double* d, doubl
   }
   double* T = P;
   for (int r = 0; r < q; ++r) {
-    HIPCHK(ctx, mm::launch_prepare(mm::KP_F64, 1, T, n, n, n, mm::PhaseScale(), prepX, op.KBT, op.MFT, s));
+    HIPCHK(ctx, mm::launch_prepare(op.lay, 1, T, n, n, n, mm::PhaseScale(), prepX, op.KBT, op.MFT, s));
     if ((st = mul(prepX, T, W)) != MM_OK) return st;
     std::swap(T, W);
   }
@@ -582,11 +685,10 @@ mm_status monitor_end(mm_ctx ctx, hipStream_t s) {
   return MM_OK;
 }
 
-// Whole run of a small expstep in one single-workgroup launch, when every
-// operator is plain FP64 / FP32, the state is small enough to stay in one
-// XCD's L2 (<= 2 MiB) and every mode fits one tile of the small-run class.
+// Several steps of an expstep whose operators all run on the resident-tile
+// kernels (or the LDS kernel of small 2-D real states): one launch per mode.
 // *used = false (and nothing launched) when the problem does not qualify.
-mm_status small_expstep(mm_ctx ctx, mm_tensor* T, const mm_op* E, int nsteps, hipStream_t s, bool* used) {
+mm_status fused_expstep(mm_ctx ctx, mm_tensor* T, const mm_op* E, int nsteps, hipStream_t s, bool* used) {
   *used = false;
   // 2-D real FP64 with both modes at most 64 long: state and operators stay
   // in one workgroup's LDS for the whole run
@@ -612,57 +714,46 @@ mm_status small_expstep(mm_ctx ctx, mm_tensor* T, const mm_op* E, int nsteps, hi
       return MM_OK;
     }
   }
-  const size_t bytes = (size_t)numel(T) * dsize(T->dtype);
-  if (bytes > ((size_t)2 << 20) || T->d > 6) return MM_OK;
-  const bool cplx = is_complex(T->dtype);
-  mm::SmallRun r;
-  std::memset(&r, 0, sizeof r);
-  r.d = T->d;
-  r.nsteps = nsteps;
-  int kp = -1;
+  // every operator on the resident-tile kernels: all steps of one mode run in
+  // one launch, the fibre tile staying in LDS between them (products along
+  // different modes commute, Section 2, so the modes' steps may be reordered)
+  double growth = 0.0;
+  bool any = false, tiny = (size_t)numel(T) * dsize(T->dtype) <= ((size_t)2 << 20);
   for (int k = 0; k < T->d; ++k) {
     if (!E[k]) continue;
-    const int p = kprec(E[k]->prec);
-    if ((p != mm::KP_F64 && p != mm::KP_F32) || (kp >= 0 && p != kp)) return MM_OK;
-    if (cplx && !E[k]->cplx) return MM_OK;   // real operator on complex planes: one launch per product
-    if (E[k]->idsplit) return MM_OK;         // identity split: one launch per product
-    kp = p;
-    mm::ModePlan plan;
-    mm::ModeArgs a;
-    mm_status st = run_mode(ctx, T->data, T->data, T->dims, T->d, T->dtype, E[k], k + 1, 0, 0, s, &plan, true,
-                            nullptr, false, &a);
-    if (st != MM_OK) {
-      ctx->err.clear();
-      return MM_OK;
-    }
-    // one row tile of the small-run class must hold all rows of the mode
-    mm::TileShape t;
-    if (!mm::tile_shape(p, SMALL_RUN_CLASS, &t)) return MM_OK;
-    const mm::FragGeom fgm = mm::frag_geom(p);
-    const int rows = t.WM * t.WMF * fgm.MB;
-    const int64_t nt = (int64_t)t.WN * t.WNF * fgm.NB;
-    if (a.Mr > rows) return MM_OK;
-    plan.grid_x = (int)((a.F + nt - 1) / nt);
-    void* prep = nullptr;
-    int KBT = 0, MFT = 0;
-    st = ensure_prepared(ctx, E[k], cplx, s, &prep, &KBT, &MFT);
-    if (st != MM_OK) return st;
-    a.A = prep;
-    r.m[k] = a;
-    r.load[k] = plan.load;
-    r.tiles[k] = plan.grid_x;
+    if (!is_res(E[k]->lay)) return MM_OK;
+    any = true;
+    growth += std::max(0.0, E[k]->log2_norm);
+    tiny = tiny && (E[k]->cplx ? 2 : 1) * E[k]->rows <= 128 && (E[k]->cplx || !is_complex(T->dtype)) && !E[k]->idsplit;
   }
-  if (kp < 0) return MM_OK;
+  if (!any) return MM_OK;
+  // steps per launch: reordered, a mode's steps may raise the state before
+  // another mode's lower it again; the modes' norm bounds keep that within
+  // 2^20 (FP32; exponent range 2^127) or 2^200 (FP64)
+  const double room = is_f64(T->dtype) ? 200.0 : 20.0;
+  const int blk = growth * nsteps <= room ? nsteps : (int)(room / growth);
+  if (blk < 2) return MM_OK;
+  // a state of at most 2 MiB with modes of at most 128 real rows is recorded
+  // as one whole run, larger ones launch by launch
+  const bool prof = ctx->profiling;
   hipEvent_t e0 = nullptr, e1 = nullptr;
-  if (ctx->profiling) {
+  if (prof && tiny) {
     HIPCHK(ctx, hipEventCreate(&e0));
     HIPCHK(ctx, hipEventCreate(&e1));
     HIPCHK(ctx, hipEventRecord(e0, s));
+    ctx->profiling = false;
   }
-  HIPCHK(ctx, mm::launch_small_run(kp, cplx ? 1 : 0, r, nullptr, s));
-  if (ctx->profiling) {
+  mm_status st = MM_OK;
+  for (int it = 0; it < nsteps && st == MM_OK; it += blk)
+    for (int k = 0; k < T->d && st == MM_OK; ++k)
+      if (E[k])
+        st = run_mode(ctx, T->data, T->data, T->dims, T->d, T->dtype, E[k], k + 1, 0, 0, s, nullptr, false, nullptr,
+                      false, false, std::min(blk, nsteps - it));
+  ctx->profiling = prof;
+  if (st != MM_OK) return st;
+  if (prof && tiny) {
     HIPCHK(ctx, hipEventRecord(e1, s));
-    ctx->recs.push_back({kp * 1000 + (cplx ? 100 : 0) + 90, e0, e1});
+    ctx->recs.push_back({(is_f64(T->dtype) ? mm::KP_F64 : mm::KP_F32) * 1000 + (is_complex(T->dtype) ? 100 : 0) + 90, e0, e1});
   }
   *used = true;
   return MM_OK;
@@ -777,6 +868,8 @@ mm_status mm_destroy(mm_ctx ctx) {
   if (ctx->bexec) hipGraphExecDestroy(ctx->bexec);
   if (ctx->bgraph) hipGraphDestroy(ctx->bgraph);
   if (ctx->bitems) hipFree(ctx->bitems);
+  if (ctx->rargs) hipFree(ctx->rargs);
+  if (ctx->ritems) hipFree(ctx->ritems);
   if (ctx->cap_stream) hipStreamDestroy(ctx->cap_stream);
   if (ctx->red_partial) hipFree(ctx->red_partial);
   if (ctx->red_result) hipFree(ctx->red_result);
@@ -823,6 +916,45 @@ mm_status mm_op_prepare_ex(mm_ctx ctx, const mm_matrix* M, mm_prec prec, unsigne
   }
   for (double v : host)
     if (!std::isfinite(v)) return fail(ctx, MM_ERR_NONFINITE, "operator holds NaN / Inf");
+  std::vector<double> rsum(M->rows, 0.0);
+  double cmax = 0.0;
+  for (int64_t j = 0; j < M->cols; ++j) {
+    double c = 0.0;
+    for (int64_t i = 0; i < M->rows; ++i) {
+      const double* v = &host[((size_t)j * M->rows + i) * comps];
+      const double m = cplx ? std::sqrt(v[0] * v[0] + v[1] * v[1]) : std::fabs(v[0]);
+      c += m;
+      rsum[i] += m;
+    }
+    cmax = std::max(cmax, c);
+  }
+  // Form of a complex operator on the resident-tile kernels.  Square ones with
+  // ||L - I||_F < 1.22 ||L||_F run on L - I in three products and add the
+  // input back; others run as they are, FP32 in four products.  Why: the third
+  // product rounds at the size of |x + y|, where the block form rounds at that
+  // of its result.  Relative L2 errors in FP32 against 64 bits (block form /
+  // three products on L / on L - I), by the ratio of the norms: GPE n = 100,
+  // four steps, ratio 0.05: 4.2e-7 / 6.3e-7 / 1.5e-7; vortex n = 99, five
+  // steps, 1.01: 4.6e-7 / 5.8e-7 / 3.1e-7; free Schroedinger, two steps,
+  // n = 200, 1.09: 4.0e-7 / 4.2e-7 / 2.9e-7, n = 256, 1.44: 3.2e-7 / 3.9e-7 /
+  // 4.0e-7.  FP64 keeps three products there too (the same runs agree with 64
+  // bits as far as that reference reaches, 5e-15 both ways).
+  bool res_id = false, res_c4 = false;
+  if (cplx && is_res(op_layout(prec, M->rows, M->cols, cplx))) {
+    if (M->rows == M->cols && !idsplit) {
+      double all = 0.0, off = 0.0;
+      for (int64_t j = 0; j < M->cols; ++j)
+        for (int64_t i = 0; i < M->rows; ++i) {
+          const double* v = &host[((size_t)j * M->rows + i) * 2];
+          const double dr = i == j ? v[0] - 1.0 : v[0];
+          all += v[0] * v[0] + v[1] * v[1];
+          off += dr * dr + v[1] * v[1];
+        }
+      res_id = off < 1.5 * all;
+    }
+    res_c4 = prec == MM_PREC_FP32 && !res_id && !idsplit;
+  }
+  const double rmax = *std::max_element(rsum.begin(), rsum.end());
   if (idsplit)   // L - I in FP64: the products carry only the departure from identity
     for (int64_t i = 0; i < M->rows; ++i) host[((size_t)i * M->rows + i) * comps] -= 1.0;
   double amax = 0.0;
@@ -833,9 +965,13 @@ mm_status mm_op_prepare_ex(mm_ctx ctx, const mm_matrix* M, mm_prec prec, unsigne
   op->cplx = cplx;
   op->prec = prec;
   op->idsplit = idsplit ? 1 : 0;
+  op->res_id = res_id ? 1 : 0;
+  op->res_c4 = res_c4 ? 1 : 0;
+  op->log2_norm = (cmax > 0.0 && rmax > 0.0) ? 0.5 * (std::log2(cmax) + std::log2(rmax)) : 0.0;
   op->a_exp = prec == MM_PREC_SPLIT_FP16X2 ? mm::fp16x2_op_exp(amax) : 0;
   const int kp = kprec(prec);
-  mm::op_blocks(kp, comps * M->rows, comps * M->cols, &op->KBT, &op->MFT);
+  op->lay = op_layout(prec, M->rows, M->cols, cplx);
+  layout_blocks(op->lay, M->rows, M->cols, cplx, &op->KBT, &op->MFT);
   // the three-product form of a complex split operator is prepared with it
   // (no product call allocates): Re L, Im L and Re L + Im L
   const bool gauss = cplx && !idsplit && (kp == mm::KP_FP16X2 || kp == mm::KP_BF16X3);
@@ -847,7 +983,7 @@ mm_status mm_op_prepare_ex(mm_ctx ctx, const mm_matrix* M, mm_prec prec, unsigne
     mm::gauss_blocks(op->rows, op->cols, &op->JBT_g, &op->MFT_g);
   }
   if (hipMalloc((void**)&op->dev_master, host.size() * sizeof(double)) != hipSuccess ||
-      hipMalloc(&op->prep, mm::prepared_bytes(kp, op->KBT, op->MFT)) != hipSuccess ||
+      hipMalloc(&op->prep, mm::prepared_bytes(op->lay, op->KBT, op->MFT)) != hipSuccess ||
       (gauss && hipMalloc(&op->prep_g, mm::gauss_prepared_bytes(kp, op->JBT_g, op->MFT_g)) != hipSuccess)) {
     if (op->dev_master) hipFree(op->dev_master);
     if (op->prep) hipFree(op->prep);
@@ -856,7 +992,9 @@ mm_status mm_op_prepare_ex(mm_ctx ctx, const mm_matrix* M, mm_prec prec, unsigne
   }
   ctx->ops.push_back(op);
   HIPCHK(ctx, hipMemcpy(op->dev_master, host.data(), host.size() * sizeof(double), hipMemcpyHostToDevice));
-  HIPCHK(ctx, mm::launch_prepare(kp, cplx, op->dev_master, op->rows, op->cols, op->rows, mm::PhaseScale(),
+  mm::PhaseScale ph;
+  ph.minus_id = op->res_id;
+  HIPCHK(ctx, mm::launch_prepare(op->lay, cplx, op->dev_master, op->rows, op->cols, op->rows, ph,
                                  op->prep, op->KBT, op->MFT, 0, op->a_exp));
   if (gauss)
     HIPCHK(ctx, mm::launch_prepare_gauss(kp, op->dev_master, op->rows, op->cols, op->rows, op->prep_g, op->JBT_g,
@@ -923,7 +1061,7 @@ mm_status mumode_expstep(mm_ctx ctx, mm_tensor* T, const mm_op* E, int nsteps, m
   if (!ctx->keep_chain || T->data != ctx->chain_end) ctx->chain_end = nullptr;
   if (ctx->small_run && nsteps >= 2 && ctx->mon_every <= 0) {
     bool used = false;
-    st = small_expstep(ctx, T, E, nsteps, (hipStream_t)stream, &used);
+    st = fused_expstep(ctx, T, E, nsteps, (hipStream_t)stream, &used);
     if (st != MM_OK || used) return st;
   }
   st = monitor_begin(ctx, nsteps);
@@ -1181,7 +1319,7 @@ mm_status ho_strang_step(mm_ctx ctx, mm_tensor* psi, const mm_op* Phi_fwd, const
   size_t per_step = 0;
   for (int k = 0; k < psi->d; ++k) {
     const mm_op_s& L = ctx->ho[k].op;
-    need[k] = (mm::prepared_bytes(kprec(L.prec), L.KBT, L.MFT) + 255) / 256 * 256;
+    need[k] = (mm::prepared_bytes(L.lay, L.KBT, L.MFT) + 255) / 256 * 256;
     per_step += need[k];
   }
   int blk = eps != 0.0 ? std::min(nsteps, 32) : 1;
@@ -1201,7 +1339,7 @@ mm_status ho_strang_step(mm_ctx ctx, mm_tensor* psi, const mm_op* Phi_fwd, const
     }
   }
   auto prepare_block = [&](int it0, int steps) -> mm_status {
-    // one launch per precision group of modes
+    // one launch per operator layout
     bool done[MM_MAXD] = {false};
     for (int k0 = 0; k0 < psi->d; ++k0) {
       if (done[k0]) continue;
@@ -1211,7 +1349,7 @@ mm_status ho_strang_step(mm_ctx ctx, mm_tensor* psi, const mm_op* Phi_fwd, const
       p.tau = tau;
       p.eps = eps;
       for (int k = k0; k < psi->d && p.modes < mm::MAX_STEP_MODES; ++k) {
-        if (done[k] || ctx->ho[k].op.prec != ctx->ho[k0].op.prec) continue;
+        if (done[k] || ctx->ho[k].op.lay != ctx->ho[k0].op.lay) continue;
         const mm_op_s& L = ctx->ho[k].op;
         mm::StepPrepMode& m = p.m[p.modes++];
         m.master = L.dev_master;
@@ -1224,7 +1362,7 @@ mm_status ho_strang_step(mm_ctx ctx, mm_tensor* psi, const mm_op* Phi_fwd, const
         m.a_exp = L.a_exp;
         done[k] = true;
       }
-      HIPCHK(ctx, mm::launch_prepare_steps(kprec(ctx->ho[k0].op.prec), p, s));
+      HIPCHK(ctx, mm::launch_prepare_steps(ctx->ho[k0].op.lay, p, s));
     }
     return MM_OK;
   };
@@ -1371,8 +1509,12 @@ mm_status mumode_expstep_batched(mm_ctx ctx, int count, mm_tensor* const* T, con
     // build the work items: per mode, one group per kernel (precision,
     // complexity, load path, tile class); every product runs in place
     std::vector<mm::BatchItem> items;
+    std::vector<mm::ResArgs> rargs;
+    std::vector<mm::ResItem> ritems;
     std::vector<mm_ctx_s::BatchGroup> groups;
     for (int k = 0; k < MM_MAXD; ++k) {
+      std::vector<mm::ResItem> byres[2];   // FP64, FP32: one entry per instance (tile: its tile count)
+      size_t lds[2] = {0, 0};
       std::vector<std::pair<uint64_t, std::vector<mm::BatchItem>>> byk;
       std::vector<mm::ModePlan> plans;
       for (int i = 0; i < count; ++i) {
@@ -1386,9 +1528,21 @@ mm_status mumode_expstep_batched(mm_ctx ctx, int count, mm_tensor* const* T, con
                       nullptr, true);
         ctx->force_cls = keep_force;
         if (st != MM_OK) return st;
-        if (!plan.covers_all_rows || plan.load == mm::KL_GENERIC)
+        if (!plan.covers_all_rows || plan.load == mm::KL_GENERIC || (is_complex(T[i]->dtype) && T[i]->dims[k] > 256))
           return fail(ctx, MM_ERR_UNSUPPORTED, "batched step needs n_mu <= 256 (complex) / 512 (real) and "
                                                "aligned fibres (instance %d, mode %d)", i, k + 1);
+        if (is_res(L->lay)) {
+          const int w = L->lay == mm::KY_RES64 ? 0 : 1;
+          mm::ResArgs a = res_args(T[i]->data, T[i]->data, T[i]->dims, T[i]->d, T[i]->dtype, L, k + 1, 0, 0);
+          int kind = 0;
+          int64_t tiles = 0;
+          size_t need = 0;
+          mm::res_batch_plan(w ? mm::KP_F32 : mm::KP_F64, res_form(L, T[i]->dtype), &a, &kind, &tiles, &need);
+          lds[w] = std::max(lds[w], need);
+          byres[w].push_back(mm::ResItem{(int)rargs.size(), kind, tiles});
+          rargs.push_back(a);
+          continue;
+        }
         void* prep = nullptr;
         int KBT = 0, MFT = 0;
         st = ensure_prepared(ctx, L, is_complex(T[i]->dtype), s, &prep, &KBT, &MFT);
@@ -1437,23 +1591,28 @@ mm_status mumode_expstep_batched(mm_ctx ctx, int count, mm_tensor* const* T, con
                          [](const mm::BatchItem& x, const mm::BatchItem& y) {
                            return (int64_t)x.a.Kr * x.a.Mr > (int64_t)y.a.Kr * y.a.Mr;
                          });
-        groups.push_back({plans[g], (int)(byk[g].first & 1), (int)items.size(), (int)byk[g].second.size()});
+        groups.push_back({plans[g], (int)(byk[g].first & 1), (int)items.size(), (int)byk[g].second.size(), 0});
         items.insert(items.end(), byk[g].second.begin(), byk[g].second.end());
       }
-    }
-    if (items.size() > ctx->bitems_cap) {
-      if (ctx->bitems) {
-        HIPCHK(ctx, hipDeviceSynchronize());
-        HIPCHK(ctx, hipFree(ctx->bitems));
-        ctx->bitems = nullptr;
-        ctx->bitems_cap = 0;
+      for (int w = 0; w < 2; ++w) {
+        if (byres[w].empty()) continue;
+        std::stable_sort(byres[w].begin(), byres[w].end(), [&](const mm::ResItem& x, const mm::ResItem& y) {
+          return res_tile_cost(rargs[x.arg], x.kind) > res_tile_cost(rargs[y.arg], y.kind);
+        });
+        mm::ModePlan plan = {};
+        plan.res = 1;
+        plan.prec = w ? mm::KP_F32 : mm::KP_F64;
+        const size_t first = ritems.size();
+        for (const mm::ResItem& x : byres[w])
+          for (int64_t tx = 0; tx < x.tile; ++tx) ritems.push_back(mm::ResItem{x.arg, x.kind, tx});
+        groups.push_back({plan, 0, (int)first, (int)(ritems.size() - first), lds[w]});
       }
-      if (hipMalloc((void**)&ctx->bitems, items.size() * sizeof(mm::BatchItem)) != hipSuccess)
-        return fail(ctx, MM_ERR_NOMEM, "batch work items");
-      ctx->bitems_cap = items.size();
     }
     HIPCHK(ctx, hipStreamSynchronize(s));
-    HIPCHK(ctx, hipMemcpy(ctx->bitems, items.data(), items.size() * sizeof(mm::BatchItem), hipMemcpyHostToDevice));
+    if ((st = upload(ctx, &ctx->bitems, &ctx->bitems_cap, items)) != MM_OK ||
+        (st = upload(ctx, &ctx->rargs, &ctx->rargs_cap, rargs)) != MM_OK ||
+        (st = upload(ctx, &ctx->ritems, &ctx->ritems_cap, ritems)) != MM_OK)
+      return st;
     ctx->bgroups = groups;
     // capture one step (all modes, all groups) as a graph
     if (ctx->bexec) {
@@ -1469,7 +1628,12 @@ mm_status mumode_expstep_batched(mm_ctx ctx, int count, mm_tensor* const* T, con
     HIPCHK(ctx, hipStreamBeginCapture(ctx->cap_stream, hipStreamCaptureModeThreadLocal));
     hipError_t le = hipSuccess;
     for (const auto& g : ctx->bgroups) {
-      le = mm::launch_mode_batch_merged(g.plan.prec, g.ida, ctx->bitems + g.offset, g.count, ctx->cap_stream);
+      if (g.plan.res)
+        le = g.plan.prec == mm::KP_F64
+                 ? mm::launch_res_batch_f64(ctx->rargs, ctx->ritems + g.offset, g.count, g.lds, ctx->cap_stream)
+                 : mm::launch_res_batch_f32(ctx->rargs, ctx->ritems + g.offset, g.count, g.lds, ctx->cap_stream);
+      else
+        le = mm::launch_mode_batch_merged(g.plan.prec, g.ida, ctx->bitems + g.offset, g.count, ctx->cap_stream);
       if (le != hipSuccess) break;
     }
     hipGraph_t graph = nullptr;
@@ -1650,11 +1814,14 @@ mm_status mm_autotune(mm_ctx ctx, const mm_tensor* T, const mm_op* E, int budget
     // tile shape is fastest, so that choice is recorded under its own key
     const bool with_pro = cplx && L->cplx;
     const double per_cand_ms = per_mode_ms / cands.size() / (with_pro ? 2 : 1);
+    std::array<int64_t, 6> key{};
     for (int pass = 0; pass < (with_pro ? 2 : 1); ++pass) {
       const double s_pre = pass ? 1e-3 : 0.0;
+      // (the resident-tile kernels finish the phase before their products
+      // start: the plain choice stands)
+      if (pass && is_res(L->lay)) cands = {ctx->tune[key].first};
       int best = -1;
       double best_ms = 0.0;
-      std::array<int64_t, 6> key{};
       for (int c : cands) {
         ctx->force_cls = c;
         mm::ModePlan plan;
@@ -1723,7 +1890,8 @@ mm_status mm_autotune_batched(mm_ctx ctx, int count, mm_tensor* const* T, const 
   for (int i = 0; i < count; ++i) {
     if (!T || !T[i] || !E || !E[i]) return fail(ctx, MM_ERR_ARG, "T / E entry %d is NULL", i);
     for (int k = 0; k < T[i]->d && k < MM_MAXD; ++k)
-      if (E[i][k]) present[k][is_complex(T[i]->dtype) ? 1 : 0] = true;
+      // the resident-tile kernels take their shape from the operator alone
+      if (E[i][k] && !is_res(E[i][k]->lay)) present[k][is_complex(T[i]->dtype) ? 1 : 0] = true;
   }
   for (int k = 0; k < MM_MAXD; ++k) ctx->batch_cls[k][0] = ctx->batch_cls[k][1] = -1;
   batch_invalidate(ctx);
@@ -1908,7 +2076,6 @@ mm_status mumode_magnus_step(mm_ctx ctx, mm_tensor* T, const mm_matrix* B, const
   HIPCHK(ctx, hipSetDevice(ctx->device));
   ctx->chain_end = nullptr;
   hipStream_t s = (hipStream_t)stream;
-  const int kp = kprec(prec);
   // per-mode device state: FP64 complex master, diagonal, exponential,
   // prepared exponential
   struct Mode {
@@ -1982,7 +2149,7 @@ mm_status mumode_magnus_step(mm_ctx ctx, mm_tensor* T, const mm_matrix* B, const
       HIPCHK(ctx, hipMemcpy(M.dd, dg[k], sizeof(double) * n, hipMemcpyHostToDevice));
     }
     M.op = scratch_op(n, prec, 0);
-    if (hipMalloc(&M.P, mm::prepared_bytes(kp, M.op.KBT, M.op.MFT)) != hipSuccess)
+    if (hipMalloc(&M.P, mm::prepared_bytes(M.op.lay, M.op.KBT, M.op.MFT)) != hipSuccess)
       return fail(ctx, MM_ERR_NOMEM, "prepared operator");
   }
   const size_t bytes = (size_t)numel(T) * dsize(T->dtype);
@@ -2019,7 +2186,7 @@ mm_status mumode_magnus_step(mm_ctx ctx, mm_tensor* T, const mm_matrix* B, const
         } else {
           M.op.a_exp = 0;
         }
-        HIPCHK(ctx, mm::launch_prepare(kp, 1, M.E, M.n, M.n, M.n, mm::PhaseScale(), M.P, M.op.KBT, M.op.MFT, s,
+        HIPCHK(ctx, mm::launch_prepare(M.op.lay, 1, M.E, M.n, M.n, M.n, mm::PhaseScale(), M.P, M.op.KBT, M.op.MFT, s,
                                        M.op.a_exp));
       }
       mm::ModePlan plan;
