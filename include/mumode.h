@@ -371,9 +371,7 @@ mm_status mm_tune_load(mm_ctx ctx, const char* path);
  *     of a mode in one launch, the fibres staying on chip between them
  *     (products along different modes commute, so the modes' steps may be
  *     reordered; blocks of steps keep intermediate growth within 2^20 in FP32,
- *     2^200 in FP64, by the operators' norms); 2-D real FP64 states with both
- *     modes at most 64 long run all steps in one single-workgroup launch.  0
- *     uses one launch per product.
+ *     2^200 in FP64, by the operators' norms).  0 uses one launch per product.
  *   MM_OPT_MONITOR_EVERY (default 0 = off): mumode_expstep and
  *     gpe_strang_step record the FP64 sum |T|^2 (the discrete mass without the
  *     cell volume, §2) after every `value` steps and after the last one, on

@@ -18,6 +18,12 @@ void res_kernel(ResArgs a) {
   res_tile<PR, FORM, MF, NF, PH>(a, blockIdx.x, blockIdx.y, lds);
 }
 
+template <int PR, int FORM, int KR>
+__global__ __launch_bounds__(256) void res_run_kernel(ResArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  res_run_tile<PR, FORM, KR>(a, blockIdx.x, lds);
+}
+
 template <int PR>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 void res_batch_kernel(const ResArgs* __restrict__ args,
@@ -52,8 +58,20 @@ ResFn res_fn(int mf) {
   }
 }
 
+template <int PR, int FORM>
+ResFn res_run_fn(int rows) {
+  return rows == 32 ? &res_run_kernel<PR, FORM, 32> : &res_run_kernel<PR, FORM, 64>;
+}
+
 template <int PR>
 ResFn res_pick(const ResPlan& p) {
+  if (p.run) {
+#if MM_RES_C4
+    if (p.form == RF_C4) return res_run_fn<PR, RF_C4>(p.run);
+#endif
+    return p.form == RF_C3 ? res_run_fn<PR, RF_C3>(p.run)
+                           : (p.form == RF_RC ? res_run_fn<PR, RF_RC>(p.run) : res_run_fn<PR, RF_RR>(p.run));
+  }
   if (p.form == RF_C3) return p.ph ? res_fn<PR, RF_C3, 1, true>(p.mf) : res_fn<PR, RF_C3, 1, false>(p.mf);
 #if MM_RES_C4
   if (p.form == RF_C4) return p.ph ? res_fn<PR, RF_C4, 1, true>(p.mf) : res_fn<PR, RF_C4, 1, false>(p.mf);

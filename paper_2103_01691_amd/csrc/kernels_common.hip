@@ -525,6 +525,22 @@ int num_classes(int prec) {
 // in one workgroup, unless that would leave fewer than two workgroups per CU.
 void res_plan(int prec, int form, bool ph, int cls, bool split_rows, ResArgs* a, ResPlan* p) {
   const int frags = (a->m + 15) / 16;
+  const int es = (prec == KP_F64 ? 8 : 4) * (form == RF_RR ? 1 : 2);
+  p->run = 0;
+  if (a->nsteps > 1 && a->n <= 64) {
+    p->run = a->n <= 32 ? 32 : 64;
+    p->prec = prec;
+    p->form = form;
+    p->mf = p->nf = 1;
+    p->ph = 0;
+    a->WM = frags;
+    a->WN = a->NRB = 1;
+    p->threads = 64 * frags;
+    p->grid_x = (int)((a->F + 15) / 16);
+    p->grid_y = 1;
+    p->lds = (size_t)2 * p->run * 17 * es;
+    return;
+  }
   int mf = cls >= 0 ? std::min(cls, 3) + 1
                     : (frags <= 4 ? 1 : (frags <= 8 ? 2 : (frags <= 12 ? 3 : (frags <= 16 ? 2 : 4))));
   if (split_rows) mf = 1;
@@ -539,7 +555,6 @@ void res_plan(int prec, int form, bool ph, int cls, bool split_rows, ResArgs* a,
   while (a->WN > 1 && (a->F + 16 * p->nf * a->WN - 1) / (16 * p->nf * a->WN) < 512) a->WN /= 2;
   a->NRB = 1;
   const int nt = 16 * p->nf * a->WN;
-  const int es = (prec == KP_F64 ? 8 : 4) * (form == RF_RR ? 1 : 2);
   p->threads = 64 * a->WM * a->WN;
   p->grid_x = (int)((a->F + nt - 1) / nt);
   p->grid_y = split_rows ? frags : 1;

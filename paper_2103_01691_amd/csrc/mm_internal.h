@@ -164,6 +164,7 @@ inline bool res_fits(int64_t rows, int64_t cols, int cplx) {
 inline int res_lds_rows(int n) { return (n + 15) / 16 * 16 + 4; }
 struct ResPlan {
   int prec, form, mf, nf, ph, threads, grid_x, grid_y;
+  int run;               // 32 or 64 rows: the operator stays in registers over the products (0: no)
   size_t lds;
 };
 // Launch shape of one product (fills a.WM / a.WN).  cls: tile class chosen by
@@ -210,13 +211,6 @@ int num_classes(int prec);
 // start / stop (optional): events recorded by the launch itself
 hipError_t launch_mode(const ModePlan& plan, const ModeArgs& a, hipStream_t s, hipEvent_t start = nullptr,
                        hipEvent_t stop = nullptr);
-// Whole run of a 2-D real FP64 integrator (n1, n2 <= 64) in one workgroup
-// with the state and the operators resident in LDS (kern_small.hip): U
-// (n1 x n2, column-major) <- E1 U E2^T nsteps times; E1 / E2 are FP64
-// masters (ld = rows), NULL leaves that mode unchanged.
-hipError_t launch_small_lds(double* U, int n1, int n2, const double* E1, const double* E2, int nsteps,
-                            hipStream_t s);
-
 // Optional diagonal phase scaling of a complex master before conversion:
 // L'[i,j] = exp(-i rc rx2[i]) L[i,j] exp(-i cc cx2[j]); rx2 / cx2 are device
 // arrays (null = no factor).

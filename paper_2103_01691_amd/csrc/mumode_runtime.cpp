@@ -686,34 +686,10 @@ mm_status monitor_end(mm_ctx ctx, hipStream_t s) {
 }
 
 // Several steps of an expstep whose operators all run on the resident-tile
-// kernels (or the LDS kernel of small 2-D real states): one launch per mode.
+// kernels: one launch per mode.
 // *used = false (and nothing launched) when the problem does not qualify.
 mm_status fused_expstep(mm_ctx ctx, mm_tensor* T, const mm_op* E, int nsteps, hipStream_t s, bool* used) {
   *used = false;
-  // 2-D real FP64 with both modes at most 64 long: state and operators stay
-  // in one workgroup's LDS for the whole run
-  if (T->d == 2 && T->dtype == MM_R64 && T->dims[0] <= 64 && T->dims[1] <= 64) {
-    bool ok = E[0] || E[1];
-    for (int k = 0; k < 2; ++k)
-      if (E[k]) ok = ok && E[k]->prec == MM_PREC_FP64 && !E[k]->cplx && !E[k]->idsplit;
-    if (ok) {
-      hipEvent_t e0 = nullptr, e1 = nullptr;
-      if (ctx->profiling) {
-        HIPCHK(ctx, hipEventCreate(&e0));
-        HIPCHK(ctx, hipEventCreate(&e1));
-        HIPCHK(ctx, hipEventRecord(e0, s));
-      }
-      HIPCHK(ctx, mm::launch_small_lds((double*)T->data, (int)T->dims[0], (int)T->dims[1],
-                                       E[0] ? E[0]->dev_master : nullptr, E[1] ? E[1]->dev_master : nullptr, nsteps,
-                                       s));
-      if (ctx->profiling) {
-        HIPCHK(ctx, hipEventRecord(e1, s));
-        ctx->recs.push_back({mm::KP_F64 * 1000 + 91, e0, e1});
-      }
-      *used = true;
-      return MM_OK;
-    }
-  }
   // every operator on the resident-tile kernels: all steps of one mode run in
   // one launch, the fibre tile staying in LDS between them (products along
   // different modes commute, Section 2, so the modes' steps may be reordered)
@@ -734,7 +710,8 @@ mm_status fused_expstep(mm_ctx ctx, mm_tensor* T, const mm_op* E, int nsteps, hi
   const int blk = growth * nsteps <= room ? nsteps : (int)(room / growth);
   if (blk < 2) return MM_OK;
   // a state of at most 2 MiB with modes of at most 128 real rows is recorded
-  // as one whole run, larger ones launch by launch
+  // as one whole run (kind 91: 2-D real FP64, both modes at most 64 long),
+  // larger ones launch by launch
   const bool prof = ctx->profiling;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (prof && tiny) {
@@ -753,7 +730,9 @@ mm_status fused_expstep(mm_ctx ctx, mm_tensor* T, const mm_op* E, int nsteps, hi
   if (st != MM_OK) return st;
   if (prof && tiny) {
     HIPCHK(ctx, hipEventRecord(e1, s));
-    ctx->recs.push_back({(is_f64(T->dtype) ? mm::KP_F64 : mm::KP_F32) * 1000 + (is_complex(T->dtype) ? 100 : 0) + 90, e0, e1});
+    const bool d2 = T->d == 2 && T->dtype == MM_R64 && T->dims[0] <= 64 && T->dims[1] <= 64;
+    ctx->recs.push_back({(is_f64(T->dtype) ? mm::KP_F64 : mm::KP_F32) * 1000 + (is_complex(T->dtype) ? 100 : 0) +
+                             (d2 ? 91 : 90), e0, e1});
   }
   *used = true;
   return MM_OK;

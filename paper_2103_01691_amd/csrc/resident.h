@@ -97,70 +97,14 @@ __device__ __forceinline__ void vortex_phase(T& re, T& im, T hs, T wi) {
   re = r;
 }
 
-// One tile: fibres [tile * NT, + NT), rows of the NRB row blocks (WM * MF
-// fragments of 16 rows each) from block rowblk * NRB on, one after the other.
-// FORM: RF_C3, RF_RC, RF_RR.  PH: the instance carries the phases.  lds:
-// res_lds_rows(n) rows of NT + 1 entries.
-template <int PR, int FORM, int MF, int NF, bool PH>
-__device__ __forceinline__ void res_tile(const ResArgs& a, int64_t tile, int rowblk, void* lds) {
-  typedef RTr<PR> T;
-  typedef typename T::st st;
-  typedef typename T::st2 st2;
-  typedef typename T::unit unit;
-  typedef typename T::acc acc_t;
-  constexpr bool CX = FORM != RF_RR;                 // complex entries
-  constexpr bool AC = FORM == RF_C3 || FORM == RF_C4;   // complex operator
-  typedef typename std::conditional<CX, st2, st>::type ent;
-  constexpr int NP = FORM == RF_C3 ? 3 : (CX ? 2 : 1);   // accumulators per output fragment
-  constexpr int UK = (int)(16 / ((AC ? 2 : 1) * sizeof(st)));       // K-blocks per operator unit
-  constexpr int D = UK == 4 ? 2 : (MF == 1 ? 4 : (MF == 2 && sizeof(st) == 4 ? 3 : 2));   // operator ring depth in units
-  constexpr int U = 8;                               // staging loads in flight per thread
-
+// Stage the NT fibres from f0 (rows 0 .. K4 - 1, zero from row n on and for
+// fibres past the last one): put(row, fibre, entry, weight of the fibre).
+template <typename ent, bool PH, typename Put>
+__device__ __forceinline__ void res_stage(const ResArgs& a, int64_t f0, int nthr, int NT, int K4, Put&& put) {
+  constexpr int U = 8;   // loads in flight per thread
   const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave % a.WM, wn = wave / a.WM;
-  const int nthr = 64 * a.WM * a.WN;
-  const int NT = 16 * NF * a.WN;
-  const int ld = NT + 1;
-  const int K4 = (a.n + 4 * UK - 1) / (4 * UK) * (4 * UK);   // rows of whole units, zero from n on
-  const int64_t f0 = tile * NT;
-  ent* L = (ent*)lds;
-  const ent* in = (const ent*)a.in;
   const int n = a.n;
-
-  // operator: fragment mf0 + i, unit ku at Ap + i * 64 + ku * ustride (the
-  // prepared operator is padded by MF - 1 fragments and D units)
-  const int64_t ustride = (int64_t)a.MFT * 64;
-  const int KU = K4 / (4 * UK);
-  int mf0 = 0;                           // first row fragment of this wave
-  const unit* __restrict__ Ap = nullptr;
-  unit ring[D][MF];
-  auto preload = [&](int rb) {
-    mf0 = ((rowblk * a.NRB + rb) * a.WM + wm) * MF;
-    Ap = (const unit*)a.A + (int64_t)min(mf0, a.MFT - MF) * 64 + lane;
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-#pragma unroll
-      for (int i = 0; i < MF; ++i) ring[d][i] = Ap[i * 64];
-      Ap += ustride;
-    }
-  };
-
-  if constexpr (!PH) preload(0);         // (with phases their registers come first)
-
-  // ---------------------------------------------------------------- staging
-  auto put = [&](int k, int f, ent v, double wf) {
-    if constexpr (PH) {
-      if (a.s_pre != 0.0) {
-        st re = v[0], im = v[1];
-        if (a.winv) vortex_phase<st>(re, im, (st)(0.5 * a.s_pre), (st)(wf * a.winv[(int64_t)a.wmu * 4096 + min(k, n - 1)]));
-        else phase<st>(re, im, (st)a.s_pre);
-        v = st2{re, im};
-      }
-    }
-    L[k * ld + f] = v;
-  };
+  const ent* in = (const ent*)a.in;
   if (a.P == 1) {
     // contiguous fibres: 16 lanes along K
     const int kk = tid & 15;
@@ -210,23 +154,114 @@ __device__ __forceinline__ void res_tile(const ResArgs& a, int64_t tile, int row
         if (k0 + kstep * u < K4) put(k0 + kstep * u, f, v[u], wf);
     }
   }
+}
+
+// The MFMAs of K-block u of operator unit au on fibre entries x.
+template <int FORM, typename acc_t, int NP, typename unit, typename ent>
+__device__ __forceinline__ void res_mac(acc_t (&acc)[NP], const unit& au, int u, const ent& x) {
+  if constexpr (FORM == RF_C3) {
+    rmfma(acc[0], au[2 * u], x[0]);
+    rmfma(acc[1], au[2 * u + 1], x[1]);
+    rmfma(acc[2], au[2 * u] + au[2 * u + 1], x[0] + x[1]);
+  } else if constexpr (FORM == RF_C4) {
+    rmfma(acc[0], au[2 * u], x[0]);
+    rmfma(acc[1], au[2 * u], x[1]);
+    rmfma(acc[0], -au[2 * u + 1], x[1]);
+    rmfma(acc[1], au[2 * u + 1], x[0]);
+  } else if constexpr (FORM == RF_RC) {
+    rmfma(acc[0], au[u], x[0]);
+    rmfma(acc[1], au[u], x[1]);
+  } else {
+    rmfma(acc[0], au[u], x);
+  }
+}
+// The output entry of accumulator register r (logical row 4 g + r of the
+// fragment in both precisions: the FP64 rows are permuted at preparation).
+template <int FORM, typename ent, typename acc_t, int NP>
+__device__ __forceinline__ ent res_out(const acc_t (&acc)[NP], int r) {
+  if constexpr (FORM == RF_C3) return ent{acc[0][r] - acc[1][r], acc[2][r] - (acc[0][r] + acc[1][r])};
+  else if constexpr (NP == 2) return ent{acc[0][r], acc[1][r]};
+  else return acc[0][r];
+}
+
+// One tile: fibres [tile * NT, + NT), rows of the NRB row blocks (WM * MF
+// fragments of 16 rows each) from block rowblk * NRB on, one after the other.
+// FORM: RF_C3, RF_RC, RF_RR.  PH: the instance carries the phases.  lds:
+// res_lds_rows(n) rows of NT + 1 entries.
+template <int PR, int FORM, int MF, int NF, bool PH>
+__device__ __forceinline__ void res_tile(const ResArgs& a, int64_t tile, int rowblk, void* lds) {
+  typedef RTr<PR> T;
+  typedef typename T::st st;
+  typedef typename T::st2 st2;
+  typedef typename T::unit unit;
+  typedef typename T::acc acc_t;
+  constexpr bool CX = FORM != RF_RR;                 // complex entries
+  constexpr bool AC = FORM == RF_C3 || FORM == RF_C4;   // complex operator
+  typedef typename std::conditional<CX, st2, st>::type ent;
+  constexpr int NP = FORM == RF_C3 ? 3 : (CX ? 2 : 1);   // accumulators per output fragment
+  constexpr int UK = (int)(16 / ((AC ? 2 : 1) * sizeof(st)));       // K-blocks per operator unit
+  constexpr int D = UK == 4 ? 2 : (MF == 1 ? 4 : (MF == 2 && sizeof(st) == 4 ? 3 : 2));   // operator ring depth in units
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave % a.WM, wn = wave / a.WM;
+  const int nthr = 64 * a.WM * a.WN;
+  const int NT = 16 * NF * a.WN;
+  const int ld = NT + 1;
+  const int K4 = (a.n + 4 * UK - 1) / (4 * UK) * (4 * UK);   // rows of whole units, zero from n on
+  const int64_t f0 = tile * NT;
+  ent* L = (ent*)lds;
+  const int n = a.n;
+
+  // operator: fragment mf0 + i, unit ku at Ap + i * 64 + ku * ustride (the
+  // prepared operator is padded by MF - 1 fragments and D units)
+  const int64_t ustride = (int64_t)a.MFT * 64;
+  const int KU = K4 / (4 * UK);
+  int mf0 = 0;                           // first row fragment of this wave
+  const unit* __restrict__ Ap = nullptr;
+  unit ring[D][MF];
+  auto preload = [&](int rb) {
+    mf0 = ((rowblk * a.NRB + rb) * a.WM + wm) * MF;
+    Ap = (const unit*)a.A + (int64_t)min(mf0, a.MFT - MF) * 64 + lane;
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+#pragma unroll
+      for (int i = 0; i < MF; ++i) ring[d][i] = Ap[i * 64];
+      Ap += ustride;
+    }
+  };
+
+  if constexpr (!PH) preload(0);         // (with phases their registers come first)
+
+  res_stage<ent, PH>(a, f0, nthr, NT, K4, [&](int k, int f, ent v, double wf) {
+    if constexpr (PH) {
+      if (a.s_pre != 0.0) {
+        st re = v[0], im = v[1];
+        if (a.winv) vortex_phase<st>(re, im, (st)(0.5 * a.s_pre), (st)(wf * a.winv[(int64_t)a.wmu * 4096 + min(k, n - 1)]));
+        else phase<st>(re, im, (st)a.s_pre);
+        v = st2{re, im};
+      }
+    }
+    L[k * ld + f] = v;
+  });
   __syncthreads();
 
   // ---------------------------------------------------------------- product
   const int g = lane >> 4, c = lane & 15;
   const int fl0 = wn * 16 * NF + c;      // this lane's fibre in N-fragment 0
-  acc_t acc[NP][MF][NF];
+  acc_t acc[MF][NF][NP];
   const ent* const Lb = L + g * ld + fl0;
   ent b[2][NF];
   // one product of the tile: fibre entries one K-block ahead from LDS,
   // operator units D ahead from L2
   auto product = [&]() {
 #pragma unroll
-    for (int t = 0; t < NP; ++t)
+    for (int i = 0; i < MF; ++i)
 #pragma unroll
-      for (int i = 0; i < MF; ++i)
+      for (int j = 0; j < NF; ++j)
 #pragma unroll
-        for (int j = 0; j < NF; ++j) acc[t][i][j] = acc_t{0, 0, 0, 0};
+        for (int t = 0; t < NP; ++t) acc[i][j][t] = acc_t{0, 0, 0, 0};
     const ent* Lk = Lb;
 #pragma unroll
     for (int j = 0; j < NF; ++j) b[0][j] = Lk[16 * j];
@@ -244,38 +279,9 @@ __device__ __forceinline__ void res_tile(const ResArgs& a, int64_t tile, int row
             __builtin_amdgcn_sched_barrier(0);
             const ent(&x)[NF] = b[s];
 #pragma unroll
-            for (int i = 0; i < MF; ++i) {
-              if constexpr (FORM == RF_C3) {
-                const st ar = ring[d][i][2 * u], ai = ring[d][i][2 * u + 1];
-                const st as = ar + ai;
+            for (int i = 0; i < MF; ++i)
 #pragma unroll
-                for (int j = 0; j < NF; ++j) {
-                  rmfma(acc[0][i][j], ar, x[j][0]);
-                  rmfma(acc[1][i][j], ai, x[j][1]);
-                  rmfma(acc[2][i][j], as, x[j][0] + x[j][1]);
-                }
-              } else if constexpr (FORM == RF_C4) {
-                const st ar = ring[d][i][2 * u], ai = ring[d][i][2 * u + 1];
-#pragma unroll
-                for (int j = 0; j < NF; ++j) {
-                  rmfma(acc[0][i][j], ar, x[j][0]);
-                  rmfma(acc[1][i][j], ar, x[j][1]);
-                  rmfma(acc[0][i][j], -ai, x[j][1]);
-                  rmfma(acc[1][i][j], ai, x[j][0]);
-                }
-              } else if constexpr (FORM == RF_RC) {
-                const st ar = ring[d][i][u];
-#pragma unroll
-                for (int j = 0; j < NF; ++j) {
-                  rmfma(acc[0][i][j], ar, x[j][0]);
-                  rmfma(acc[1][i][j], ar, x[j][1]);
-                }
-              } else {
-                const st ar = ring[d][i][u];
-#pragma unroll
-                for (int j = 0; j < NF; ++j) rmfma(acc[0][i][j], ar, x[j]);
-              }
-            }
+              for (int j = 0; j < NF; ++j) res_mac<FORM>(acc[i][j], ring[d][i], u, x[j]);
             __builtin_amdgcn_sched_barrier(0);
           }
 #pragma unroll
@@ -289,18 +295,8 @@ __device__ __forceinline__ void res_tile(const ResArgs& a, int64_t tile, int row
       }
     }
   };
-  // result entry of accumulator register r (logical row 4 g + r of the
-  // fragment in both precisions: the FP64 rows are permuted at preparation)
   auto result = [&](int i, int j, int r, int row) -> ent {
-    ent y;
-    if constexpr (FORM == RF_C3) {
-      const st t1 = acc[0][i][j][r], t2 = acc[1][i][j][r];
-      y = st2{t1 - t2, (st)acc[NP - 1][i][j][r] - (t1 + t2)};
-    } else if constexpr (CX) {
-      y = st2{acc[0][i][j][r], acc[NP - 1][i][j][r]};
-    } else {
-      y = acc[0][i][j][r];
-    }
+    ent y = res_out<FORM, ent>(acc[i][j], r);
     if (a.idadd) y += L[row * ld + fl0 + 16 * j];
     return y;
   };
@@ -359,6 +355,92 @@ __device__ __forceinline__ void res_tile(const ResArgs& a, int64_t tile, int row
           }
         }
     }
+  }
+}
+
+// nsteps products of one square operator of at most KR rows on a tile of 16
+// fibres, one wave per 16 rows, the operator in registers and the tile
+// ping-ponging between two LDS buffers (one barrier per product).  Such runs
+// leave one wave per SIMD, so a product is latency: its KR / 4 K-blocks are
+// fully unrolled with the padding in place (no branch between them), all LDS
+// reads run ahead of the first MFMA, and even and odd K-blocks accumulate
+// apart, so that consecutive MFMAs do not wait for each other.  us per call,
+// 20 steps: 2-D heat 64 x 64 FP64 36 (101 with the state and both operators in
+// one workgroup's LDS, 52 through res_tile), n = 64 C3 FP32 104 (125 through
+// res_tile).
+template <int PR, int FORM, int KR>
+__device__ __forceinline__ void res_run_tile(const ResArgs& a, int64_t tile, void* lds) {
+  typedef RTr<PR> T;
+  typedef typename T::st st;
+  typedef typename T::st2 st2;
+  typedef typename T::unit unit;
+  typedef typename T::acc acc_t;
+  constexpr bool CX = FORM != RF_RR;
+  constexpr bool AC = FORM == RF_C3 || FORM == RF_C4;
+  typedef typename std::conditional<CX, st2, st>::type ent;
+  constexpr int NP = FORM == RF_C3 ? 3 : (CX ? 2 : 1);
+  constexpr int UK = (int)(16 / ((AC ? 2 : 1) * sizeof(st)));
+  constexpr int KUM = KR / (4 * UK);
+  constexpr int ld = 17;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // row fragment
+  const int n = a.n;
+  const int KU = (n + 4 * UK - 1) / (4 * UK);
+  const int64_t f0 = tile * 16;
+  ent* cur = (ent*)lds;
+  ent* nxt = cur + KR * ld;
+  unit op[KUM];
+#pragma unroll
+  for (int ku = 0; ku < KUM; ++ku) {
+    op[ku] = unit{};
+    if (ku < KU) op[ku] = ((const unit*)a.A)[((int64_t)ku * a.MFT + wave) * 64 + lane];
+  }
+  res_stage<ent, false>(a, f0, 64 * a.WM, 16, KR, [&](int k, int f, ent v, double) {
+    cur[k * ld + f] = v;
+    if (k >= n) nxt[k * ld + f] = v;     // the padding rows of both buffers are zero
+  });
+  __syncthreads();
+  const int g = lane >> 4, c = lane & 15;
+  const int row0 = 16 * wave + 4 * g;
+  for (int s = 1;; ++s) {
+    acc_t acc[2][NP];
+#pragma unroll
+    for (int t = 0; t < NP; ++t) acc[0][t] = acc[1][t] = acc_t{0, 0, 0, 0};
+    const ent* Lk = cur + g * ld + c;
+    ent b[KR / 4];
+#pragma unroll
+    for (int kb = 0; kb < KR / 4; ++kb) b[kb] = Lk[4 * kb * ld];
+    __builtin_amdgcn_sched_barrier(0);   // every read is issued before the first MFMA waits
+#pragma unroll
+    for (int kb = 0; kb < KR / 4; ++kb) res_mac<FORM>(acc[kb & 1], op[kb / UK], kb % UK, b[kb]);
+#pragma unroll
+    for (int t = 0; t < NP; ++t) acc[0][t] += acc[1][t];
+    ent y[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      y[r] = res_out<FORM, ent>(acc[0], r);
+      if (a.idadd) y[r] += cur[min(row0 + r, n - 1) * ld + c];
+    }
+    if (s >= a.nsteps) {
+      const int64_t fg = f0 + c;
+      if (fg < a.F) {
+        int64_t p = 0, q = fg;
+        if (a.P != 1) fibre_pq(fg, a.P, a.F, &p, &q);
+        ent* dst = (ent*)a.out + (p + a.P * (int64_t)n * q);
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (row0 + r < n) dst[(int64_t)(row0 + r) * a.P] = y[r];
+      }
+      return;
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (row0 + r < n) nxt[(row0 + r) * ld + c] = y[r];
+    __syncthreads();
+    ent* t = cur;
+    cur = nxt;
+    nxt = t;
   }
 }
 
