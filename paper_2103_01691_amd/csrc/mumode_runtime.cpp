@@ -325,7 +325,7 @@ mm::ResArgs res_args(const void* in, void* out, const int64_t* dims, int d, mm_d
 mm_status run_mode(mm_ctx ctx, const void* in, void* out, const int64_t* dims, int d, mm_dtype dt,
                    mm_op L, int mu, double s_pre, double s_post, hipStream_t s, mm::ModePlan* plan_out,
                    bool dry, const void* prep_override = nullptr, bool batch = false,
-                   bool split_rows = false, int nsteps = 1) {
+                   bool split_rows = false, int nsteps = 1, const double* winv = nullptr) {
   // A real operator on a complex state (with no fused phase) acts on the
   // (re, im) planes separately: the state is then the real tensor
   // (2, n_1, ..., n_d) and mode mu its mode mu + 1, i.e. two real fibres per
@@ -379,6 +379,12 @@ mm_status run_mode(mm_ctx ctx, const void* in, void* out, const int64_t* dims, i
     mm::ResArgs r = res_args(in, out, dims, d, dt, L, mu, s_pre, s_post);
     if (prep_override) r.A = prep_override;
     r.nsteps = nsteps;
+    if (winv && is_complex(dt)) {
+      r.winv = winv;
+      r.wd = d;
+      r.wmu = mu - 1;
+      for (int k = 0; k < d; ++k) r.wdims[k] = dims[k];
+    }
     mm::ModePlan plan = {};
     plan.prec = kprec(L->prec);
     plan.cplx = cplx ? 1 : 0;
@@ -504,7 +510,9 @@ void batch_invalidate(mm_ctx ctx) {
 // Tucker sweep over the modes with per-mode ops (square), in place on T.
 // first_pre / last_post: phase coefficients fused into the first / last
 // applied product (0 = none).
-mm_status sweep(mm_ctx ctx, mm_tensor* T, const mm_op* E, double first_pre, double last_post, hipStream_t s) {
+// winv: the phases are the vortex problem's (resident-tile operators only).
+mm_status sweep(mm_ctx ctx, mm_tensor* T, const mm_op* E, double first_pre, double last_post, hipStream_t s,
+                const double* winv = nullptr) {
   int first = -1, last = -1;
   for (int k = 0; k < T->d; ++k)
     if (E[k]) {
@@ -526,7 +534,7 @@ mm_status sweep(mm_ctx ctx, mm_tensor* T, const mm_op* E, double first_pre, doub
       dst = (cur == T->data) ? ctx->ws : T->data;
     }
     st = run_mode(ctx, cur, dst, T->dims, T->d, T->dtype, E[k], k + 1, k == first ? first_pre : 0.0,
-                  k == last ? last_post : 0.0, s, nullptr, false);
+                  k == last ? last_post : 0.0, s, nullptr, false, nullptr, false, false, 1, winv);
     if (st != MM_OK) return st;
     cur = dst;
   }
@@ -1425,11 +1433,21 @@ mm_status vortex_strang_step(mm_ctx ctx, mm_tensor* v, const mm_op* E, const dou
   }
   const int f64 = is_f64(v->dtype) ? 1 : 0;
   // merged steps N(tau/2) [L N(tau)]^(nsteps-1) L N(tau/2): N keeps |v|, so
-  // adjacent half steps compose; each N is one pass over the state (its
+  // adjacent half steps compose.  The resident-tile kernels apply each N while
+  // they stage the next step's first product, the last one as they write the
+  // results (n = 81 FP64: MEASURED us per step against MEASURED with a pass of
+  // its own); the split precisions make one pass over the state for each (its
   // coefficient depends on the position through W^-1).  FP16X2: a rotation
   // raises a component by at most sqrt(2), which the state scale's headroom
   // covers (as for the fused prologue phase), so the running bound of the
   // last product carries over the pass to the next step's first product
+  if (is_res(E[0]->lay) && is_res(E[v->d - 1]->lay)) {
+    for (int it = 0; it < nsteps; ++it) {
+      st = sweep(ctx, v, E, it == 0 ? 0.5 * tau : tau, it + 1 < nsteps ? 0.0 : 0.5 * tau, s, ctx->winv);
+      if (st != MM_OK) return st;
+    }
+    return MM_OK;
+  }
   HIPCHK(ctx, mm::launch_vortex_phase(v->data, f64, v->d, v->dims, ctx->winv, 0.5 * tau, s));
   for (int it = 0; it < nsteps; ++it) {
     st = sweep(ctx, v, E, 0.0, 0.0, s);
