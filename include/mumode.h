@@ -279,8 +279,9 @@ mm_status mumode_expstep_batched(mm_ctx ctx, int count, mm_tensor* const* T, con
  *            g[2*(n*d + k)] = Re g_{k+1}(t_n + tau/2); may be NULL when no
  *            mode has a time-dependent part.  The caller evaluates them.
  * T is complex (MM_C128 with MM_PREC_FP64, MM_C64 otherwise), in place.
- * Allocates per-call device buffers (freed before returning, which
- * synchronises the device). */
+ * The exponentials of up to 32 steps are formed together ahead of their
+ * products.  Uses buffers of the context (grown as needed) and synchronises
+ * the device before returning. */
 mm_status mumode_magnus_step(mm_ctx ctx, mm_tensor* T, const mm_matrix* B, const double* const* d, const double* g,
                              double tau, int nsteps, mm_prec prec, mm_stream stream);
 

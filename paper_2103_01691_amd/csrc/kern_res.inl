@@ -15,7 +15,7 @@ template <int PR, int FORM, int MF, int NF, bool PH>
 __global__ __launch_bounds__(MF == 1 ? 1024 : 512)
 void res_kernel(ResArgs a) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
-  res_tile<PR, FORM, MF, NF, PH>(a, blockIdx.x, blockIdx.y, lds);
+  res_tile<PR, FORM, MF, NF, PH>(a, blockIdx.x, lds);
 }
 
 template <int PR, int FORM, int KR>
@@ -33,7 +33,7 @@ void res_batch_kernel(const ResArgs* __restrict__ args,
   const ResArgs& a = args[it.arg];
   switch (it.kind) {
 #define MM_RK(F_, M_) \
-  case F_ * 10 + M_: res_tile<PR, F_, M_, 1, false>(a, it.tile, 0, lds); break;
+  case F_ * 10 + M_: res_tile<PR, F_, M_, 1, false>(a, it.tile, lds); break;
     MM_RK(RF_C3, 1) MM_RK(RF_C3, 2) MM_RK(RF_C3, 3) MM_RK(RF_C3, 4)
 #if MM_RES_C4
     MM_RK(RF_C4, 1) MM_RK(RF_C4, 2) MM_RK(RF_C4, 3) MM_RK(RF_C4, 4)
@@ -88,7 +88,7 @@ hipError_t res_launch(const ResPlan& p, const ResArgs& a, hipStream_t s, hipEven
     const hipError_t e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds);
     if (e != hipSuccess) return e;
   }
-  const dim3 grid(p.grid_x, p.grid_y), block(p.threads);
+  const dim3 grid(p.grid_x), block(p.threads);
   if (start || stop) hipExtLaunchKernelGGL(fn, grid, block, p.lds, s, start, stop, 0, a);
   else hipLaunchKernelGGL(fn, grid, block, p.lds, s, a);
   return hipGetLastError();

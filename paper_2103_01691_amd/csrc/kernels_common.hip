@@ -192,6 +192,14 @@ __global__ void prepare_kernel(const double* __restrict__ master, int64_t rows, 
                   MFT, a_exp);
 }
 
+// The operators of a batch of matrix exponentials (blockIdx.y: job).
+template <int LY>
+__global__ void prepare_jobs_kernel(ExpmBatch b, const double* __restrict__ exps, int KBT, int MFT) {
+  const ExpmJob& j = b.j[blockIdx.y];
+  prepare_any<LY>((int64_t)blockIdx.x * blockDim.x + threadIdx.x, exps + (int64_t)blockIdx.y * b.n * b.n * 2, b.n, b.n,
+                  b.n, 1, PhaseScale(), j.out, KBT, MFT, j.a_exp);
+}
+
 // Per-step operators of the time-dependent harmonic-oscillator splitting
 // (blockIdx.y = step * modes + entry).
 template <int PR>
@@ -345,16 +353,6 @@ __global__ void expm_generator_kernel(const double* __restrict__ A, int n, const
   }
   X[2 * e] = fr * re - fi * im;
   X[2 * e + 1] = fr * im + fi * re;
-}
-
-// T = I + f W (f real); W == nullptr: T = I
-__global__ void expm_horner_kernel(double* __restrict__ T, const double* __restrict__ W, int n, double f) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= (int64_t)n * n) return;
-  const int i = (int)(e % n), j = (int)(e / n);
-  const double one = i == j ? 1.0 : 0.0;
-  T[2 * e] = one + (W ? f * W[2 * e] : 0.0);
-  T[2 * e + 1] = W ? f * W[2 * e + 1] : 0.0;
 }
 
 // P = W + c0 I + c1 X + c2 X2 + c3 X3 (W nullable): one Paterson-Stockmeyer
@@ -523,7 +521,7 @@ int num_classes(int prec) {
 // registers or fewer, so four waves fit each SIMD), four above (real
 // operators of up to 512 rows).  Short operators put several 16-fibre groups
 // in one workgroup, unless that would leave fewer than two workgroups per CU.
-void res_plan(int prec, int form, bool ph, int cls, bool split_rows, ResArgs* a, ResPlan* p) {
+void res_plan(int prec, int form, bool ph, int cls, ResArgs* a, ResPlan* p) {
   const int frags = (a->m + 15) / 16;
   const int es = (prec == KP_F64 ? 8 : 4) * (form == RF_RR ? 1 : 2);
   p->run = 0;
@@ -537,27 +535,24 @@ void res_plan(int prec, int form, bool ph, int cls, bool split_rows, ResArgs* a,
     a->WN = a->NRB = 1;
     p->threads = 64 * frags;
     p->grid_x = (int)((a->F + 15) / 16);
-    p->grid_y = 1;
     p->lds = (size_t)2 * p->run * 17 * es;
     return;
   }
   int mf = cls >= 0 ? std::min(cls, 3) + 1
                     : (frags <= 4 ? 1 : (frags <= 8 ? 2 : (frags <= 12 ? 3 : (frags <= 16 ? 2 : 4))));
-  if (split_rows) mf = 1;
   while (mf < 4 && (frags + mf - 1) / mf > (mf == 1 ? 16 : 8)) ++mf;
   p->prec = prec;
   p->form = form;
   p->mf = mf;
   p->ph = ph ? 1 : 0;
-  a->WM = split_rows ? 1 : (frags + mf - 1) / mf;
-  a->WN = split_rows ? 1 : (a->WM == 1 ? 4 : (a->WM == 2 ? 2 : 1));
+  a->WM = (frags + mf - 1) / mf;
+  a->WN = a->WM == 1 ? 4 : (a->WM == 2 ? 2 : 1);
   p->nf = (form == RF_RR && a->n <= 256 && a->F >= 16384) ? 2 : 1;
   while (a->WN > 1 && (a->F + 16 * p->nf * a->WN - 1) / (16 * p->nf * a->WN) < 512) a->WN /= 2;
   a->NRB = 1;
   const int nt = 16 * p->nf * a->WN;
   p->threads = 64 * a->WM * a->WN;
   p->grid_x = (int)((a->F + nt - 1) / nt);
-  p->grid_y = split_rows ? frags : 1;
   p->lds = (size_t)res_lds_rows(a->n) * (nt + 1) * es;
 }
 
@@ -705,6 +700,19 @@ hipError_t launch_prepare_steps(int prec, const StepPrep& p, hipStream_t s) {
   return hipGetLastError();
 }
 
+hipError_t launch_prepare_jobs(int lay, const ExpmBatch& b, const double* exps, int KBT, int MFT, hipStream_t s) {
+  if (b.nb < 1 || b.nb > MAX_EXPM) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)(((int64_t)KBT * MFT * 64 + 255) / 256), (unsigned)b.nb);
+  switch (lay) {
+#define MM_PJ(L_) \
+  case L_: hipLaunchKernelGGL(prepare_jobs_kernel<L_>, grid, dim3(256), 0, s, b, exps, KBT, MFT); break;
+    MM_PJ(KP_F64) MM_PJ(KP_F32) MM_PJ(KP_BF16X3) MM_PJ(KP_FP16X2) MM_PJ(KP_BF16) MM_PJ(KY_RES64) MM_PJ(KY_RES32)
+#undef MM_PJ
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
 hipError_t launch_prepare(int prec, int cplx, const double* master, int64_t rows, int64_t cols,
                           int64_t ld, PhaseScale ph, void* out, int KBT, int MFT, hipStream_t s,
                           int a_exp) {
@@ -751,12 +759,6 @@ hipError_t launch_expm_generator(const double* A, int n, const double* d, double
   const int64_t nn = (int64_t)n * n;
   hipLaunchKernelGGL(expm_generator_kernel, dim3((unsigned)((nn + 255) / 256)), dim3(256), 0, s, A, n, d, gr, gi, fr,
                      fi, X);
-  return hipGetLastError();
-}
-
-hipError_t launch_expm_horner(double* T, const double* W, int n, double f, hipStream_t s) {
-  const int64_t nn = (int64_t)n * n;
-  hipLaunchKernelGGL(expm_horner_kernel, dim3((unsigned)((nn + 255) / 256)), dim3(256), 0, s, T, W, n, f);
   return hipGetLastError();
 }
 

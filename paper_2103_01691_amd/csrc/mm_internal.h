@@ -163,14 +163,13 @@ inline bool res_fits(int64_t rows, int64_t cols, int cplx) {
 // LDS rows of a tile: whole operator units and one K-block that is read ahead.
 inline int res_lds_rows(int n) { return (n + 15) / 16 * 16 + 4; }
 struct ResPlan {
-  int prec, form, mf, nf, ph, threads, grid_x, grid_y;
+  int prec, form, mf, nf, ph, threads, grid_x;
   int run;               // 32 or 64 rows: the operator stays in registers over the products (0: no)
   size_t lds;
 };
 // Launch shape of one product (fills a.WM / a.WN).  cls: tile class chosen by
-// the tuner (MF = cls + 1 fragments per wave), -1 for the built-in rule;
-// split_rows: out of place, rows may be spread over workgroups.
-void res_plan(int prec, int form, bool ph, int cls, bool split_rows, ResArgs* a, ResPlan* p);
+// the tuner (MF = cls + 1 fragments per wave), -1 for the built-in rule.
+void res_plan(int prec, int form, bool ph, int cls, ResArgs* a, ResPlan* p);
 hipError_t launch_res(const ResPlan& p, const ResArgs& a, hipStream_t s, hipEvent_t start = nullptr,
                       hipEvent_t stop = nullptr);
 hipError_t launch_res_f64(const ResPlan& p, const ResArgs& a, hipStream_t s, hipEvent_t start, hipEvent_t stop);
@@ -258,12 +257,31 @@ int fp16x2_op_exp(double amax);
 // T = I); out[j] = sum_i |(A + g diag(d))_ij|.
 hipError_t launch_expm_generator(const double* A, int n, const double* d, double gr, double gi, double fr, double fi,
                                  double* X, hipStream_t s);
-hipError_t launch_expm_horner(double* T, const double* W, int n, double f, hipStream_t s);
 hipError_t launch_expm_colsum(const double* A, int n, const double* d, double gr, double gi, double* out,
                               hipStream_t s);
 // P = W + c[0] I + c[1] X + c[2] X2 + c[3] X3 (W nullable)
 hipError_t launch_expm_ps(double* P, const double* W, const double* X, const double* X2, const double* X3, int n,
                           const double* c, hipStream_t s);
+// Exponentials exp(f (A + g diag(d))) of up to MAX_EXPM matrices of one size
+// n <= EXPM_MAX_N with a common number q of squarings (kern_expm.hip); buf:
+// expm_batch_bytes(n, nb).  *result: job z's exponential at z * n * n entries.
+constexpr int MAX_EXPM = 32;
+constexpr int EXPM_MAX_N = 256;
+struct ExpmJob {
+  const double* A;
+  const double* d;         // nullable
+  double gr, gi, fr, fi;
+  void* out;               // prepared operator of launch_prepare_jobs
+  int a_exp;
+};
+struct ExpmBatch {
+  int n, nb, q;
+  ExpmJob j[MAX_EXPM];
+};
+size_t expm_batch_bytes(int n, int nb);
+hipError_t launch_expm_batch(const ExpmBatch& b, double* buf, double** result, hipStream_t s);
+// Prepare the batch's exponentials (layout lay, KBT x MFT blocks) into the jobs' outs.
+hipError_t launch_prepare_jobs(int lay, const ExpmBatch& b, const double* exps, int KBT, int MFT, hipStream_t s);
 // out = Psi diag(exp(-i tau (k + 1/2))) Phi (Phi: K x m, Psi: m x K, real
 // FP64 device masters with ld = rows; out: m x m complex FP64 interleaved).
 hipError_t launch_hermite_collapse(const double* Phi, const double* Psi, int m, int K, double tau, double* out,

@@ -92,6 +92,13 @@ struct mm_ctx_s {
   size_t ex_bytes = 0;
   void* ex_prep = nullptr;
   size_t ex_prep_bytes = 0;
+  // mumode_magnus_step: generators and diagonals (device, pinned staging),
+  // prepared exponentials of a block of steps, one exponential above EXPM_MAX_N
+  void* mg_buf = nullptr;
+  void* mg_stage = nullptr;
+  void* mg_prep = nullptr;
+  double* mg_exp = nullptr;
+  size_t mg_bytes = 0, mg_stage_bytes = 0, mg_prep_bytes = 0, mg_exp_bytes = 0;
   // per-mode scratch for operators re-prepared every step (ho_strang_step)
   void* step_prep[MM_MAXD] = {nullptr};
   size_t step_prep_bytes[MM_MAXD] = {0};
@@ -325,7 +332,7 @@ mm::ResArgs res_args(const void* in, void* out, const int64_t* dims, int d, mm_d
 mm_status run_mode(mm_ctx ctx, const void* in, void* out, const int64_t* dims, int d, mm_dtype dt,
                    mm_op L, int mu, double s_pre, double s_post, hipStream_t s, mm::ModePlan* plan_out,
                    bool dry, const void* prep_override = nullptr, bool batch = false,
-                   bool split_rows = false, int nsteps = 1, const double* winv = nullptr) {
+                   int nsteps = 1, const double* winv = nullptr) {
   // A real operator on a complex state (with no fused phase) acts on the
   // (re, im) planes separately: the state is then the real tensor
   // (2, n_1, ..., n_d) and mode mu its mode mu + 1, i.e. two real fibres per
@@ -391,12 +398,12 @@ mm_status run_mode(mm_ctx ctx, const void* in, void* out, const int64_t* dims, i
     plan.load = load;
     plan.pro = (cplx && s_pre != 0.0) ? 1 : 0;
     plan.epi = (cplx && s_post != 0.0) ? 1 : 0;
-    plan.covers_all_rows = !split_rows;
+    plan.covers_all_rows = true;
     plan.res = 1;
-    mm::res_plan(plan.prec, res_form(L, dt), plan.pro || plan.epi, force, split_rows, &r, &plan.rp);
+    mm::res_plan(plan.prec, res_form(L, dt), plan.pro || plan.epi, force, &r, &plan.rp);
     plan.cls = force >= 0 ? std::min(force, 3) : plan.rp.mf - 1;
     plan.grid_x = plan.rp.grid_x;
-    plan.grid_y = plan.rp.grid_y;
+    plan.grid_y = 1;
     plan.threads = plan.rp.threads;
     if (plan_out) *plan_out = plan;
     if (dry) return MM_OK;
@@ -534,7 +541,7 @@ mm_status sweep(mm_ctx ctx, mm_tensor* T, const mm_op* E, double first_pre, doub
       dst = (cur == T->data) ? ctx->ws : T->data;
     }
     st = run_mode(ctx, cur, dst, T->dims, T->d, T->dtype, E[k], k + 1, k == first ? first_pre : 0.0,
-                  k == last ? last_post : 0.0, s, nullptr, false, nullptr, false, false, 1, winv);
+                  k == last ? last_post : 0.0, s, nullptr, false, nullptr, false, 1, winv);
     if (st != MM_OK) return st;
     cur = dst;
   }
@@ -581,11 +588,44 @@ mm_op_s scratch_op(int n, mm_prec prec, int a_exp) {
 // matrix product is a mode-1 product of the FP64 MFMA kernel.  bound: an
 // upper bound of ||A + g diag d||_1 known to the caller, or < 0 to compute
 // it here (synchronises s).
+// Squarings that scale fa = |f| ||A + g diag d||_1 to at most 1.
+mm_status expm_squarings(mm_ctx ctx, double fa, int* q) {
+  *q = 0;
+  if (!std::isfinite(fa)) return fail(ctx, MM_ERR_NONFINITE, "matrix holds NaN / Inf");
+  if (fa > 1.0) *q = (int)std::ceil(std::log2(fa));
+  if (*q > 1000) return fail(ctx, MM_ERR_ARG, "exponent argument too large (norm %g)", fa);
+  return MM_OK;
+}
+
 mm_status expm_device(mm_ctx ctx, int n, const double* A, const double* d, double gr, double gi, double fr,
                       double fi, double bound, double* out, hipStream_t s) {
   const size_t mat = (size_t)n * n * 2;
-  mm_status st = grow(ctx, (void**)&ctx->ex_buf, &ctx->ex_bytes, sizeof(double) * (6 * mat + n));
+  const bool small = n <= mm::EXPM_MAX_N;
+  mm_status st = grow(ctx, (void**)&ctx->ex_buf, &ctx->ex_bytes,
+                      std::max(mm::expm_batch_bytes(n, 1), sizeof(double) * 6 * mat) + sizeof(double) * n);
   if (st != MM_OK) return st;
+  double* cs = ctx->ex_buf + 6 * mat;
+  if (bound < 0) {
+    HIPCHK(ctx, mm::launch_expm_colsum(A, n, d, gr, gi, cs, s));
+    std::vector<double> h(n);
+    HIPCHK(ctx, hipMemcpyAsync(h.data(), cs, sizeof(double) * n, hipMemcpyDeviceToHost, s));
+    HIPCHK(ctx, hipStreamSynchronize(s));
+    bound = 0.0;
+    for (double v : h) bound = std::max(bound, v);
+  }
+  int q = 0;
+  if ((st = expm_squarings(ctx, std::hypot(fr, fi) * bound, &q)) != MM_OK) return st;
+  if (small) {
+    mm::ExpmBatch b = {};
+    b.n = n;
+    b.nb = 1;
+    b.q = q;
+    b.j[0] = {A, d, gr, gi, fr, fi, nullptr, 0};
+    double* r = nullptr;
+    HIPCHK(ctx, mm::launch_expm_batch(b, ctx->ex_buf, &r, s));
+    HIPCHK(ctx, hipMemcpyAsync(out, r, sizeof(double) * mat, hipMemcpyDeviceToDevice, s));
+    return MM_OK;
+  }
   mm_op_s op = scratch_op(n, MM_PREC_FP64, 0);
   const size_t pb = mm::prepared_bytes(op.lay, op.KBT, op.MFT);
   st = grow(ctx, &ctx->ex_prep, &ctx->ex_prep_bytes, 2 * pb);
@@ -596,22 +636,8 @@ mm_status expm_device(mm_ctx ctx, int n, const double* A, const double* d, doubl
   double* Y = X3 + mat;     // X^4
   double* P = Y + mat;
   double* W = P + mat;
-  double* cs = W + mat;
   void* prepX = ctx->ex_prep;
   void* prepY = (char*)ctx->ex_prep + pb;
-  if (bound < 0) {
-    HIPCHK(ctx, mm::launch_expm_colsum(A, n, d, gr, gi, cs, s));
-    std::vector<double> h(n);
-    HIPCHK(ctx, hipMemcpyAsync(h.data(), cs, sizeof(double) * n, hipMemcpyDeviceToHost, s));
-    HIPCHK(ctx, hipStreamSynchronize(s));
-    bound = 0.0;
-    for (double v : h) bound = std::max(bound, v);
-  }
-  if (!std::isfinite(bound)) return fail(ctx, MM_ERR_NONFINITE, "matrix holds NaN / Inf");
-  const double fa = std::hypot(fr, fi) * bound;
-  int q = 0;
-  if (fa > 1.0) q = (int)std::ceil(std::log2(fa));
-  if (q > 1000) return fail(ctx, MM_ERR_ARG, "exponent argument too large (norm %g)", fa);
   const double sc = std::ldexp(1.0, -q);
   const int64_t dims[2] = {n, n};
   // a product of two n x n matrices has only n fibres: where the default
@@ -621,7 +647,7 @@ mm_status expm_device(mm_ctx ctx, int n, const double* A, const double* d, doubl
   auto mul = [&](const void* prep, const double* in, double* o) {
     const int keep = ctx->force_cls;
     if (few) ctx->force_cls = 3;
-    mm_status r = run_mode(ctx, in, o, dims, 2, MM_C128, &op, 1, 0, 0, s, nullptr, false, prep, false, is_res(op.lay));
+    mm_status r = run_mode(ctx, in, o, dims, 2, MM_C128, &op, 1, 0, 0, s, nullptr, false, prep);
     ctx->force_cls = keep;
     return r;
   };
@@ -733,7 +759,7 @@ mm_status fused_expstep(mm_ctx ctx, mm_tensor* T, const mm_op* E, int nsteps, hi
     for (int k = 0; k < T->d && st == MM_OK; ++k)
       if (E[k])
         st = run_mode(ctx, T->data, T->data, T->dims, T->d, T->dtype, E[k], k + 1, 0, 0, s, nullptr, false, nullptr,
-                      false, false, std::min(blk, nsteps - it));
+                      false, std::min(blk, nsteps - it));
   ctx->profiling = prof;
   if (st != MM_OK) return st;
   if (prof && tiny) {
@@ -864,6 +890,10 @@ mm_status mm_destroy(mm_ctx ctx) {
   if (ctx->mon_dev) hipFree(ctx->mon_dev);
   if (ctx->ex_buf) hipFree(ctx->ex_buf);
   if (ctx->ex_prep) hipFree(ctx->ex_prep);
+  if (ctx->mg_buf) hipFree(ctx->mg_buf);
+  if (ctx->mg_stage) hipHostFree(ctx->mg_stage);
+  if (ctx->mg_prep) hipFree(ctx->mg_prep);
+  if (ctx->mg_exp) hipFree(ctx->mg_exp);
   if (ctx->host_result) hipHostFree(ctx->host_result);
   delete ctx;
   return MM_OK;
@@ -1435,8 +1465,8 @@ mm_status vortex_strang_step(mm_ctx ctx, mm_tensor* v, const mm_op* E, const dou
   // merged steps N(tau/2) [L N(tau)]^(nsteps-1) L N(tau/2): N keeps |v|, so
   // adjacent half steps compose.  The resident-tile kernels apply each N while
   // they stage the next step's first product, the last one as they write the
-  // results (n = 81 FP64: MEASURED us per step against MEASURED with a pass of
-  // its own); the split precisions make one pass over the state for each (its
+  // results (n = 81 FP64: 58.5 us per step against 61.6 with a pass of its
+  // own); the split precisions make one pass over the state for each (its
   // coefficient depends on the position through W^-1).  FP16X2: a rotation
   // raises a component by at most sqrt(2), which the state scale's headroom
   // covers (as for the fused prologue phase), so the running bound of the
@@ -2073,135 +2103,217 @@ mm_status mumode_magnus_step(mm_ctx ctx, mm_tensor* T, const mm_matrix* B, const
   HIPCHK(ctx, hipSetDevice(ctx->device));
   ctx->chain_end = nullptr;
   hipStream_t s = (hipStream_t)stream;
-  // per-mode device state: FP64 complex master, diagonal, exponential,
-  // prepared exponential
+  // per-mode state: FP64 complex master and diagonal on the device, the
+  // prepared exponentials of a block of steps
   struct Mode {
     int n = 0;
-    double* Bd = nullptr;
-    double* dd = nullptr;
-    double* E = nullptr;
-    void* P = nullptr;
+    size_t Boff = 0, doff = 0, poff = 0, pb = 0;   // byte offsets in mg_buf / mg_prep, bytes of one operator
+    bool on = false, timed = false;
     double bnorm = 0.0, dmax = 0.0;
     // Gershgorin discs of the Hermitian part (B + B^H)/2: centres Re b_ii,
     // radii sum_{j != i} |b_ij + conj(b_ji)| / 2
     std::vector<double> hc, hr;
+    std::vector<int> aexp;   // FP16X2 scale of each prepared exponential
     mm_op_s op;
   };
   std::vector<Mode> modes(d);
+  // the buffers below belong to the context: nothing of this call may still
+  // run when it returns, also when it fails
   struct Guard {
-    std::vector<Mode>* m;
-    ~Guard() {
-      hipDeviceSynchronize();
-      for (auto& x : *m) {
-        if (x.Bd) hipFree(x.Bd);
-        if (x.dd) hipFree(x.dd);
-        if (x.E) hipFree(x.E);
-        if (x.P) hipFree(x.P);
-      }
-    }
-  } guard{&modes};
+    ~Guard() { hipDeviceSynchronize(); }
+  } guard;
+  size_t need = 0;
+  auto reserve = [&](size_t bytes) {
+    const size_t at = need;
+    need += (bytes + 255) / 256 * 256;
+    return at;
+  };
   for (int k = 0; k < d; ++k) {
     if (!B[k].data) continue;
     Mode& M = modes[k];
-    const int n = (int)T->dims[k];
-    M.n = n;
+    M.on = true;
+    M.n = (int)T->dims[k];
+    M.timed = dg && dg[k];
+    M.Boff = reserve(sizeof(double) * 2 * (size_t)M.n * M.n);
+    if (M.timed) M.doff = reserve(sizeof(double) * M.n);
+    M.op = scratch_op(M.n, prec, 0);
+    M.pb = (mm::prepared_bytes(M.op.lay, M.op.KBT, M.op.MFT) + 255) / 256 * 256;
+  }
+  if ((st = grow(ctx, &ctx->mg_buf, &ctx->mg_bytes, need)) != MM_OK) return st;
+  if (ctx->mg_stage_bytes < need) {
+    if (ctx->mg_stage) HIPCHK(ctx, hipHostFree(ctx->mg_stage));
+    ctx->mg_stage = nullptr;
+    ctx->mg_stage_bytes = 0;
+    if (hipHostMalloc(&ctx->mg_stage, need, hipHostMallocDefault) != hipSuccess)
+      return fail(ctx, MM_ERR_NOMEM, "staging of %zu bytes", need);
+    ctx->mg_stage_bytes = need;
+  }
+  for (int k = 0; k < d; ++k) {
+    Mode& M = modes[k];
+    if (!M.on) continue;
+    const int n = M.n;
     const int comps = B[k].dtype == MM_C128 ? 2 : 1;
-    std::vector<double> full((size_t)B[k].ld * n * comps), host((size_t)n * n * 2, 0.0);
-    if (B[k].on_device)
-      HIPCHK(ctx, hipMemcpy(full.data(), B[k].data, full.size() * sizeof(double), hipMemcpyDeviceToHost));
-    else
-      std::memcpy(full.data(), B[k].data, full.size() * sizeof(double));
-    std::vector<double> colsum(n, 0.0);
-    for (int j = 0; j < n; ++j)
+    std::vector<double> full;
+    const double* src = (const double*)B[k].data;
+    if (B[k].on_device) {
+      full.resize((size_t)B[k].ld * n * comps);
+      HIPCHK(ctx, hipMemcpy(full.data(), src, full.size() * sizeof(double), hipMemcpyDeviceToHost));
+      src = full.data();
+    }
+    double* host = (double*)((char*)ctx->mg_stage + M.Boff);
+    double check = 0.0;
+    for (int j = 0; j < n; ++j) {
+      const double* col = src + (size_t)j * B[k].ld * comps;
+      double* o = host + 2 * (size_t)j * n;
+      double sum = 0.0;
       for (int i = 0; i < n; ++i) {
-        const double re = full[((size_t)j * B[k].ld + i) * comps];
-        const double im = comps == 2 ? full[((size_t)j * B[k].ld + i) * 2 + 1] : 0.0;
-        if (!std::isfinite(re) || !std::isfinite(im)) return fail(ctx, MM_ERR_NONFINITE, "B[%d] holds NaN / Inf", k);
-        host[2 * ((size_t)j * n + i)] = re;
-        host[2 * ((size_t)j * n + i) + 1] = im;
-        colsum[j] += std::hypot(re, im);
+        const double re = col[(size_t)i * comps], im = comps == 2 ? col[(size_t)i * 2 + 1] : 0.0;
+        o[2 * i] = re;
+        o[2 * i + 1] = im;
+        check += 0.0 * re + 0.0 * im;   // NaN as soon as one entry is not finite
+        sum += std::sqrt(re * re + im * im);
       }
-    for (double v : colsum) M.bnorm = std::max(M.bnorm, v);
-    M.hc.assign(n, 0.0);
-    M.hr.assign(n, 0.0);
-    for (int i = 0; i < n; ++i) {
-      M.hc[i] = host[2 * ((size_t)i * n + i)];
-      for (int j = 0; j < n; ++j) {
-        if (j == i) continue;
-        const double re = host[2 * ((size_t)j * n + i)] + host[2 * ((size_t)i * n + j)];
-        const double im = host[2 * ((size_t)j * n + i) + 1] - host[2 * ((size_t)i * n + j) + 1];
-        M.hr[i] += 0.5 * std::hypot(re, im);
+      if (!std::isfinite(sum)) {        // squares out of range
+        sum = 0.0;
+        for (int i = 0; i < n; ++i) sum += std::hypot(o[2 * i], o[2 * i + 1]);
+      }
+      M.bnorm = std::max(M.bnorm, sum);
+    }
+    if (check != 0.0) return fail(ctx, MM_ERR_NONFINITE, "B[%d] holds NaN / Inf", k);
+    if (prec == MM_PREC_SPLIT_FP16X2) {
+      M.hc.assign(n, 0.0);
+      M.hr.assign(n, 0.0);
+      for (int i = 0; i < n; ++i) {
+        M.hc[i] = host[2 * ((size_t)i * n + i)];
+        for (int j = 0; j < n; ++j) {
+          if (j == i) continue;
+          const double re = host[2 * ((size_t)j * n + i)] + host[2 * ((size_t)i * n + j)];
+          const double im = host[2 * ((size_t)j * n + i) + 1] - host[2 * ((size_t)i * n + j) + 1];
+          M.hr[i] += 0.5 * std::hypot(re, im);
+        }
       }
     }
-    if (hipMalloc((void**)&M.Bd, host.size() * sizeof(double)) != hipSuccess ||
-        hipMalloc((void**)&M.E, host.size() * sizeof(double)) != hipSuccess)
-      return fail(ctx, MM_ERR_NOMEM, "mode buffers");
-    HIPCHK(ctx, hipMemcpy(M.Bd, host.data(), host.size() * sizeof(double), hipMemcpyHostToDevice));
-    if (dg && dg[k]) {
+    if (M.timed) {
+      double* dd = (double*)((char*)ctx->mg_stage + M.doff);
       for (int i = 0; i < n; ++i) {
         if (!std::isfinite(dg[k][i])) return fail(ctx, MM_ERR_NONFINITE, "d[%d] holds NaN / Inf", k);
+        dd[i] = dg[k][i];
         M.dmax = std::max(M.dmax, std::fabs(dg[k][i]));
       }
-      if (hipMalloc((void**)&M.dd, sizeof(double) * n) != hipSuccess) return fail(ctx, MM_ERR_NOMEM, "diagonal");
-      HIPCHK(ctx, hipMemcpy(M.dd, dg[k], sizeof(double) * n, hipMemcpyHostToDevice));
     }
-    M.op = scratch_op(n, prec, 0);
-    if (hipMalloc(&M.P, mm::prepared_bytes(M.op.lay, M.op.KBT, M.op.MFT)) != hipSuccess)
-      return fail(ctx, MM_ERR_NOMEM, "prepared operator");
+  }
+  if (need) HIPCHK(ctx, hipMemcpyAsync(ctx->mg_buf, ctx->mg_stage, need, hipMemcpyHostToDevice, s));
+  // the exponentials of a block of steps are formed together, ahead of its
+  // products (at most 256 MiB of prepared operators)
+  size_t fixed = 0, per_step = 0;
+  for (const Mode& M : modes)
+    if (M.on) (M.timed ? per_step : fixed) += M.pb;
+  int blk = per_step ? std::min(nsteps, 32) : nsteps;
+  while (per_step && blk > 1 && per_step * blk > ((size_t)256 << 20)) blk /= 2;
+  {
+    size_t at = 0;
+    for (Mode& M : modes)
+      if (M.on) {
+        M.poff = at;
+        at += M.pb * (M.timed ? (size_t)blk : 1);
+      }
+    if ((st = grow(ctx, &ctx->mg_prep, &ctx->mg_prep_bytes, at)) != MM_OK) return st;
   }
   const size_t bytes = (size_t)numel(T) * dsize(T->dtype);
-  for (int it = 0; it < nsteps; ++it) {
-    void* cur = T->data;
+  for (int it0 = 0; it0 < nsteps; it0 += blk) {
+    const int cnt = std::min(blk, nsteps - it0);
+    // jobs of one size, layout and number of squarings run as one batch
+    mm::ExpmBatch batch = {};
+    const mm_op_s* bop = nullptr;
+    auto flush = [&]() -> mm_status {
+      if (batch.nb == 0) return MM_OK;
+      mm_status r = grow(ctx, (void**)&ctx->ex_buf, &ctx->ex_bytes, mm::expm_batch_bytes(batch.n, batch.nb));
+      if (r != MM_OK) return r;
+      double* e = nullptr;
+      HIPCHK(ctx, mm::launch_expm_batch(batch, ctx->ex_buf, &e, s));
+      HIPCHK(ctx, mm::launch_prepare_jobs(bop->lay, batch, e, bop->KBT, bop->MFT, s));
+      batch.nb = 0;
+      return MM_OK;
+    };
     for (int k = 0; k < d; ++k) {
       Mode& M = modes[k];
-      if (!M.Bd) continue;
-      if (it == 0 || M.dd) {
-        // E_k = exp(tau (B_k + g diag d_k)) at the midpoint of the step
+      if (!M.on || (!M.timed && it0 > 0)) continue;
+      for (int j = 0; j < (M.timed ? cnt : 1); ++j) {
+        // E_k = exp(tau (B_k + g diag d_k)) at the midpoint of step it0 + j
         double gr = 0.0, gi = 0.0;
-        if (M.dd) {
-          gr = g[2 * ((size_t)it * d + k)];
-          gi = g[2 * ((size_t)it * d + k) + 1];
+        if (M.timed) {
+          gr = g[2 * ((size_t)(it0 + j) * d + k)];
+          gi = g[2 * ((size_t)(it0 + j) * d + k) + 1];
           if (!std::isfinite(gr) || !std::isfinite(gi)) return fail(ctx, MM_ERR_NONFINITE, "g not finite");
         }
         const double bound = M.bnorm + std::hypot(gr, gi) * M.dmax;
-        st = expm_device(ctx, M.n, M.Bd, M.dd, gr, gi, tau, 0.0, bound, M.E, s);
-        if (st != MM_OK) return st;
         // FP16X2 operator scale from a bound of max |E_ij|: |E_ij| <= ||E||_2
         // <= exp(tau mu(A)) with mu the logarithmic 2-norm, the largest
         // eigenvalue of the Hermitian part of A = B + g diag(d) (that part is
         // (B + B^H)/2 + Re(g) diag(d)), bounded by its Gershgorin discs; for
         // tau < 0 the same with -A.  For a skew-Hermitian (unitary-flow)
         // generator the bound is 1, the true size of the entries.
+        int a_exp = 0;
         if (prec == MM_PREC_SPLIT_FP16X2) {
           double mu = -HUGE_VAL;
           const double sg = tau >= 0.0 ? 1.0 : -1.0;
           for (int i = 0; i < M.n; ++i) {
-            const double c = M.hc[i] + (M.dd ? gr * dg[k][i] : 0.0);
+            const double c = M.hc[i] + (M.timed ? gr * dg[k][i] : 0.0);
             mu = std::max(mu, sg * c + M.hr[i]);
           }
-          M.op.a_exp = mm::fp16x2_op_exp(std::exp(std::min(700.0, std::fabs(tau) * mu)));
-        } else {
-          M.op.a_exp = 0;
+          a_exp = mm::fp16x2_op_exp(std::exp(std::min(700.0, std::fabs(tau) * mu)));
         }
-        HIPCHK(ctx, mm::launch_prepare(M.op.lay, 1, M.E, M.n, M.n, M.n, mm::PhaseScale(), M.P, M.op.KBT, M.op.MFT, s,
-                                       M.op.a_exp));
+        if ((int)M.aexp.size() <= j) M.aexp.resize(j + 1);
+        M.aexp[j] = a_exp;
+        const double* A = (const double*)((char*)ctx->mg_buf + M.Boff);
+        const double* dd = M.timed ? (const double*)((char*)ctx->mg_buf + M.doff) : nullptr;
+        void* out = (char*)ctx->mg_prep + M.poff + (size_t)j * M.pb;
+        if (M.n > mm::EXPM_MAX_N) {
+          const size_t eb = sizeof(double) * 2 * (size_t)M.n * M.n;
+          if ((st = grow(ctx, (void**)&ctx->mg_exp, &ctx->mg_exp_bytes, eb)) != MM_OK) return st;
+          st = expm_device(ctx, M.n, A, dd, gr, gi, tau, 0.0, bound, ctx->mg_exp, s);
+          if (st != MM_OK) return st;
+          HIPCHK(ctx, mm::launch_prepare(M.op.lay, 1, ctx->mg_exp, M.n, M.n, M.n, mm::PhaseScale(), out, M.op.KBT,
+                                         M.op.MFT, s, a_exp));
+          continue;
+        }
+        int q = 0;
+        if ((st = expm_squarings(ctx, std::fabs(tau) * bound, &q)) != MM_OK) return st;
+        const int cap = (int)std::max<size_t>(1, std::min<size_t>(mm::MAX_EXPM, ((size_t)64 << 20) / mm::expm_batch_bytes(M.n, 1)));
+        if (batch.nb && (batch.n != M.n || batch.q != q || bop->lay != M.op.lay || batch.nb >= cap))
+          if ((st = flush()) != MM_OK) return st;
+        batch.n = M.n;
+        batch.q = q;
+        bop = &M.op;
+        batch.j[batch.nb++] = {A, dd, gr, gi, tau, 0.0, out, a_exp};
       }
-      mm::ModePlan plan;
-      st = run_mode(ctx, cur, cur, T->dims, d, T->dtype, &M.op, k + 1, 0, 0, s, &plan, true, M.P);
-      if (st != MM_OK) return st;
-      void* dst = cur;
-      if (!plan.covers_all_rows) {
-        st = ensure_ws(ctx, bytes);
-        if (st != MM_OK) return st;
-        dst = (cur == T->data) ? ctx->ws : T->data;
-      }
-      st = run_mode(ctx, cur, dst, T->dims, d, T->dtype, &M.op, k + 1, 0, 0, s, nullptr, false, M.P);
-      if (st != MM_OK) return st;
-      cur = dst;
     }
-    if (cur != T->data) {
-      HIPCHK(ctx, hipMemcpyAsync(T->data, cur, bytes, hipMemcpyDeviceToDevice, s));
-      if (ctx->chain_end == cur) ctx->chain_end = T->data;
+    if ((st = flush()) != MM_OK) return st;
+    for (int it = it0; it < it0 + cnt; ++it) {
+      void* cur = T->data;
+      for (int k = 0; k < d; ++k) {
+        Mode& M = modes[k];
+        if (!M.on) continue;
+        const int j = M.timed ? it - it0 : 0;
+        const void* P = (char*)ctx->mg_prep + M.poff + (size_t)j * M.pb;
+        M.op.a_exp = M.aexp[j];
+        mm::ModePlan plan;
+        st = run_mode(ctx, cur, cur, T->dims, d, T->dtype, &M.op, k + 1, 0, 0, s, &plan, true, P);
+        if (st != MM_OK) return st;
+        void* dst = cur;
+        if (!plan.covers_all_rows) {
+          st = ensure_ws(ctx, bytes);
+          if (st != MM_OK) return st;
+          dst = (cur == T->data) ? ctx->ws : T->data;
+        }
+        st = run_mode(ctx, cur, dst, T->dims, d, T->dtype, &M.op, k + 1, 0, 0, s, nullptr, false, P);
+        if (st != MM_OK) return st;
+        cur = dst;
+      }
+      if (cur != T->data) {
+        HIPCHK(ctx, hipMemcpyAsync(T->data, cur, bytes, hipMemcpyDeviceToDevice, s));
+        if (ctx->chain_end == cur) ctx->chain_end = T->data;
+      }
     }
   }
   return MM_OK;

@@ -184,12 +184,12 @@ __device__ __forceinline__ ent res_out(const acc_t (&acc)[NP], int r) {
   else return acc[0][r];
 }
 
-// One tile: fibres [tile * NT, + NT), rows of the NRB row blocks (WM * MF
-// fragments of 16 rows each) from block rowblk * NRB on, one after the other.
+// One tile: fibres [tile * NT, + NT), all rows, in NRB blocks of WM * MF
+// fragments of 16 rows, one after the other.
 // FORM: RF_C3, RF_RC, RF_RR.  PH: the instance carries the phases.  lds:
 // res_lds_rows(n) rows of NT + 1 entries.
 template <int PR, int FORM, int MF, int NF, bool PH>
-__device__ __forceinline__ void res_tile(const ResArgs& a, int64_t tile, int rowblk, void* lds) {
+__device__ __forceinline__ void res_tile(const ResArgs& a, int64_t tile, void* lds) {
   typedef RTr<PR> T;
   typedef typename T::st st;
   typedef typename T::st2 st2;
@@ -222,7 +222,7 @@ __device__ __forceinline__ void res_tile(const ResArgs& a, int64_t tile, int row
   const unit* __restrict__ Ap = nullptr;
   unit ring[D][MF];
   auto preload = [&](int rb) {
-    mf0 = ((rowblk * a.NRB + rb) * a.WM + wm) * MF;
+    mf0 = (rb * a.WM + wm) * MF;
     Ap = (const unit*)a.A + (int64_t)min(mf0, a.MFT - MF) * 64 + lane;
 #pragma unroll
     for (int d = 0; d < D; ++d) {
