@@ -598,6 +598,38 @@ hipError_t launch_prepare_gauss(int prec, const double* master, int64_t rows, in
   return hipGetLastError();
 }
 
+bool rs_plan(const ModeArgs& a, int prec, ModePlan* plan) {
+  if (a.Mr > 512 || a.Kr > 512) return false;
+  const int kb = (a.Kr + 15) / 16;
+  const int npb = prec == KP_BF16X3 ? 3 : 2;
+  auto lds = [&](int nf) { return (size_t)kb * nf * npb * 1024; };
+  // 64 fibres per tile, 32 where that would leave CUs without one or not fit
+  // the 160 KiB of LDS
+  const int nf = (lds(2) <= 160 * 1024 && a.F >= 64 * 200 && (prec != KP_BF16X3 || a.Mr <= 256)) ? 2 : 1;
+  *plan = ModePlan{};
+  plan->cls = RS_CLASS;
+  plan->rs = nf;
+  plan->rs_lds = std::max<size_t>(lds(nf), 256);
+  plan->nt = 32 * nf;
+  plan->mt_rows = 512;
+  plan->grid_x = (int)((a.F + 32 * nf - 1) / (32 * nf));
+  plan->grid_y = 1;
+  plan->threads = 64 * ((a.Mr + 31) / 32);
+  plan->covers_all_rows = true;
+  return plan->grid_x > 0;
+}
+
+namespace {
+// Whether the built-in choice for a complex split product is class 6: always
+// where the other classes gather unaligned fibres entry by entry (FP16X2 n = 81
+// 9.6 us against 15.7, n = 141 30 against 39-42), and up to 200 entries on
+// aligned ones (mode 2, class 6 / best other built-in choice, us: n = 48
+// 6.1 / 9.3, 64 7.0 / 9.4, 128 17.0 / 16.8, 192 60 / 73; BF16X3 64 5.3 / 9.8,
+// 192 80 / 109).  Above, its 32- and 64-fibre tiles stream the operator too
+// often (n = 224 103 / 81, 256 138 / 106).
+bool rs_rule(const ModeArgs& a, int load) { return load == KL_GENERIC || (a.Mr <= 400 && a.Kr <= 400); }
+}  // namespace
+
 bool plan_mode(const ModeArgs& a, int prec, int cplx, bool want_pro, bool want_epi, bool fcontig_ok,
                bool kcontig_ok, ModePlan* plan, bool batch, int force_cls, bool gauss_ok) {
   FragGeom g = frag_geom(prec);
@@ -620,6 +652,17 @@ bool plan_mode(const ModeArgs& a, int prec, int cplx, bool want_pro, bool want_e
   // (three-product classes: their own padding, a multiple of every chunk)
   int kbt = 0, mft = 0;
   op_blocks(prec, a.Mr, a.Kr, &kbt, &mft);
+  // resident-tile split kernel (class 6): any stride, at most 256 complex
+  // rows and columns
+  if (split && cplx && !batch && (force_cls == RS_CLASS || (force_cls < 0 && rs_rule(a, load))) &&
+      rs_plan(a, prec, plan)) {
+    plan->prec = prec;
+    plan->cplx = cplx;
+    plan->load = load;
+    plan->pro = pro;
+    plan->epi = epi;
+    return true;
+  }
   if (force_cls >= 0 && tile_shape(prec, force_cls, &tf) && (is_gauss_class(force_cls) || kbt % tf.KCH == 0) &&
       (batch ? batch_kind_any(prec, cplx, load, force_cls)
              : pick_kernel_any(prec, cplx, load, pro, epi, force_cls) != nullptr)) {
@@ -657,7 +700,11 @@ bool plan_mode(const ModeArgs& a, int prec, int cplx, bool want_pro, bool want_e
   return plan->grid_x > 0 && pick_kernel_any(prec, cplx, load, pro, epi, cls) != nullptr;
 }
 
-hipError_t launch_mode(const ModePlan& p, const ModeArgs& a, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
+hipError_t launch_mode(const ModePlan& p, const ModeArgs& a, hipStream_t s, hipEvent_t start, hipEvent_t stop,
+                       const VortexW* w) {
+  if (p.rs)
+    return p.prec == KP_FP16X2 ? launch_rsplit_fp16x2(p, a, w ? *w : VortexW{}, s, start, stop)
+                               : launch_rsplit_bf16x3(p, a, w ? *w : VortexW{}, s, start, stop);
   KernFn fn = pick_kernel_any(p.prec, p.cplx, p.load, p.pro, p.epi, p.cls, p.full, a.idadd ? 1 : 0);
   if (!fn) return hipErrorInvalidDeviceFunction;
   dim3 grid(p.grid_x, p.grid_y, 1);

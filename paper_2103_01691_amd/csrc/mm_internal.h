@@ -136,6 +136,14 @@ hipError_t launch_mode_batch_merged(int prec, int ida, const BatchItem* items, i
 // operator x state: complex x complex in three or four real products, real x
 // complex, real x real
 enum ResForm { RF_C3 = 0, RF_RC = 1, RF_RR = 2, RF_C4 = 3 };
+// Position-dependent phase exp((i s/2)(1 - W^-1 |v|^2)) in place of the Gross-
+// Pitaevskii one: W^-1 = prod_j winv[j * 4096 + i_j] over the wd modes of
+// lengths wdims; wmu is the (0-based) mode of the product.  winv null: none.
+struct VortexW {
+  const double* winv;
+  int wd, wmu;
+  int64_t wdims[6];
+};
 struct ResArgs {
   const void* in;
   void* out;
@@ -148,12 +156,7 @@ struct ResArgs {
   int nsteps;            // products applied to the resident tile (square operators; 1 otherwise)
   int idadd;             // the operator holds L - I: add the input back
   double s_pre, s_post;  // phase coefficients (0: none)
-  // position-dependent phase exp((i s/2)(1 - W^-1 |v|^2)) instead of the
-  // Gross-Pitaevskii one: W^-1 = prod_j winv[j * 4096 + i_j] over the wd modes
-  // of lengths wdims; wmu is the (0-based) mode of this product
-  const double* winv;
-  int wd, wmu;
-  int64_t wdims[6];
+  VortexW w;
 };
 // Longest operator side of the resident kernels.
 inline bool res_fits(int64_t rows, int64_t cols, int cplx) {
@@ -194,9 +197,20 @@ struct ModePlan {
   bool covers_all_rows;
   int full;            // every tile complete and output offsets fit 32 bits
   int gauss;           // three-product kernel: the operator's Gauss preparation
+  int rs = 0;          // resident-tile split kernel (class 6): N-fragments per tile
+  size_t rs_lds = 0;
   int res = 0;         // resident-tile kernel (FP64 / FP32; rp is its launch shape)
   ResPlan rp;
 };
+
+// Resident-tile kernels of the complex split products (rsplit.h), tile class 6
+// of FP16X2 and BF16X3: modes of at most 256 complex entries.
+constexpr int RS_CLASS = 6;
+bool rs_plan(const ModeArgs& a, int prec, ModePlan* plan);
+hipError_t launch_rsplit_fp16x2(const ModePlan& p, const ModeArgs& a, const VortexW& w, hipStream_t s, hipEvent_t start,
+                                hipEvent_t stop);
+hipError_t launch_rsplit_bf16x3(const ModePlan& p, const ModeArgs& a, const VortexW& w, hipStream_t s, hipEvent_t start,
+                                hipEvent_t stop);
 
 // Fill `plan` for the given problem; returns false if no kernel fits.
 // batch: plan for the batched work-list kernel (tile classes 0..2 only).
@@ -207,9 +221,10 @@ bool plan_mode(const ModeArgs& a, int prec, int cplx, bool want_pro, bool want_e
                bool gauss_ok = false);
 // Number of tile classes of a precision (classes 0 .. n-1).
 int num_classes(int prec);
-// start / stop (optional): events recorded by the launch itself
+// start / stop (optional): events recorded by the launch itself; w: vortex
+// phase (class 6 only)
 hipError_t launch_mode(const ModePlan& plan, const ModeArgs& a, hipStream_t s, hipEvent_t start = nullptr,
-                       hipEvent_t stop = nullptr);
+                       hipEvent_t stop = nullptr, const VortexW* w = nullptr);
 // Optional diagonal phase scaling of a complex master before conversion:
 // L'[i,j] = exp(-i rc rx2[i]) L[i,j] exp(-i cc cx2[j]); rx2 / cx2 are device
 // arrays (null = no factor).

@@ -380,18 +380,20 @@ mm_status run_mode(mm_ctx ctx, const void* in, void* out, const int64_t* dims, i
     }
     if (it != ctx->tune.end()) force = it->second.first;
   }
+  mm::VortexW vw = {};
+  if (winv && is_complex(dt)) {
+    vw.winv = winv;
+    vw.wd = d;
+    vw.wmu = mu - 1;
+    for (int k = 0; k < d; ++k) vw.wdims[k] = dims[k];
+  }
   if (is_res(L->lay)) {
     // resident-tile kernel: the complex entries themselves are the fibres'
     // entries (no real view), any P
     mm::ResArgs r = res_args(in, out, dims, d, dt, L, mu, s_pre, s_post);
     if (prep_override) r.A = prep_override;
     r.nsteps = nsteps;
-    if (winv && is_complex(dt)) {
-      r.winv = winv;
-      r.wd = d;
-      r.wmu = mu - 1;
-      for (int k = 0; k < d; ++k) r.wdims[k] = dims[k];
-    }
+    r.w = vw;
     mm::ModePlan plan = {};
     plan.prec = kprec(L->prec);
     plan.cplx = cplx ? 1 : 0;
@@ -459,7 +461,7 @@ mm_status run_mode(mm_ctx ctx, const void* in, void* out, const int64_t* dims, i
     ctx->chain_end = out;
   }
   const int kind = plan.prec * 1000 + plan.cplx * 100 + plan.load * 10 + plan.pro * 2 + plan.epi;
-  return timed_launch(ctx, kind, [&](hipEvent_t e0, hipEvent_t e1) { return mm::launch_mode(plan, a, s, e0, e1); });
+  return timed_launch(ctx, kind, [&](hipEvent_t e0, hipEvent_t e1) { return mm::launch_mode(plan, a, s, e0, e1, &vw); });
 }
 
 mm_status ensure_ws(mm_ctx ctx, size_t bytes) {
@@ -517,7 +519,7 @@ void batch_invalidate(mm_ctx ctx) {
 // Tucker sweep over the modes with per-mode ops (square), in place on T.
 // first_pre / last_post: phase coefficients fused into the first / last
 // applied product (0 = none).
-// winv: the phases are the vortex problem's (resident-tile operators only).
+// winv: the phases are the vortex problem's (resident-tile kernels only).
 mm_status sweep(mm_ctx ctx, mm_tensor* T, const mm_op* E, double first_pre, double last_post, hipStream_t s,
                 const double* winv = nullptr) {
   int first = -1, last = -1;
@@ -532,7 +534,8 @@ mm_status sweep(mm_ctx ctx, mm_tensor* T, const mm_op* E, double first_pre, doub
   for (int k = first; k <= last; ++k) {
     if (!E[k]) continue;
     mm::ModePlan plan;
-    mm_status st = run_mode(ctx, cur, cur, T->dims, T->d, T->dtype, E[k], k + 1, 0, 0, s, &plan, true);
+    mm_status st = run_mode(ctx, cur, cur, T->dims, T->d, T->dtype, E[k], k + 1, k == first ? first_pre : 0.0,
+                            k == last ? last_post : 0.0, s, &plan, true);
     if (st != MM_OK) return st;
     void* dst = cur;
     if (!plan.covers_all_rows) {
@@ -1466,16 +1469,25 @@ mm_status vortex_strang_step(mm_ctx ctx, mm_tensor* v, const mm_op* E, const dou
   // adjacent half steps compose.  The resident-tile kernels apply each N while
   // they stage the next step's first product, the last one as they write the
   // results (n = 81 FP64: 58.5 us per step against 61.6 with a pass of its
-  // own); the split precisions make one pass over the state for each (its
-  // coefficient depends on the position through W^-1).  FP16X2: a rotation
+  // own); the others make one pass over the state for each (its coefficient
+  // depends on the position through W^-1).  FP16X2: a rotation
   // raises a component by at most sqrt(2), which the state scale's headroom
   // covers (as for the fused prologue phase), so the running bound of the
   // last product carries over the pass to the next step's first product
-  if (is_res(E[0]->lay) && is_res(E[v->d - 1]->lay)) {
+  bool fused = true;
+  for (int k = 0; k < v->d && fused; k += std::max(1, v->d - 1)) {
+    mm::ModePlan plan;
+    st = run_mode(ctx, v->data, v->data, v->dims, v->d, v->dtype, E[k], k + 1, k == 0 ? tau : 0.0,
+                  k == v->d - 1 ? tau : 0.0, s, &plan, true);
+    if (st != MM_OK) return st;
+    fused = plan.res || plan.rs;
+  }
+  if (fused) {
     for (int it = 0; it < nsteps; ++it) {
       st = sweep(ctx, v, E, it == 0 ? 0.5 * tau : tau, it + 1 < nsteps ? 0.0 : 0.5 * tau, s, ctx->winv);
       if (st != MM_OK) return st;
     }
+    ctx->chain_end = nullptr;
     return MM_OK;
   }
   HIPCHK(ctx, mm::launch_vortex_phase(v->data, f64, v->d, v->dims, ctx->winv, 0.5 * tau, s));

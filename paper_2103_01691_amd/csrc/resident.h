@@ -72,15 +72,15 @@ __device__ __forceinline__ void fibre_pq(int64_t fg, int64_t P, int64_t F, int64
   }
 }
 
-// Inverse cell weight of fibre (p, q) without the factor of mode a.wmu.
-__device__ __forceinline__ double fibre_weight(const ResArgs& a, int64_t p, int64_t q) {
+// Inverse cell weight of fibre (p, q) without the factor of mode v.wmu.
+__device__ __forceinline__ double fibre_weight(const VortexW& v, int64_t p, int64_t q) {
   double w = 1.0;
-  for (int j = 0; j < a.wd; ++j) {
-    if (j == a.wmu) continue;
-    int64_t& r = j < a.wmu ? p : q;
-    const int64_t i = r % a.wdims[j];
-    r /= a.wdims[j];
-    w *= a.winv[(int64_t)j * 4096 + i];
+  for (int j = 0; j < v.wd; ++j) {
+    if (j == v.wmu) continue;
+    int64_t& r = j < v.wmu ? p : q;
+    const int64_t i = r % v.wdims[j];
+    r /= v.wdims[j];
+    w *= v.winv[(int64_t)j * 4096 + i];
   }
   return w;
 }
@@ -114,7 +114,7 @@ __device__ __forceinline__ void res_stage(const ResArgs& a, int64_t f0, int nthr
       const ent* src = in + (ok ? fg * n : 0);
       double wf = 0.0;
       if constexpr (PH) {
-        if (a.winv && ok) wf = fibre_weight(a, 0, fg);
+        if (a.w.winv && ok) wf = fibre_weight(a.w, 0, fg);
       }
       for (int k0 = kk; k0 < K4; k0 += 16 * U) {
         ent v[U];
@@ -139,7 +139,7 @@ __device__ __forceinline__ void res_stage(const ResArgs& a, int64_t f0, int nthr
     if (ok) fibre_pq(fg, a.P, a.F, &p, &q);
     double wf = 0.0;
     if constexpr (PH) {
-      if (a.winv && ok) wf = fibre_weight(a, p, q);
+      if (a.w.winv && ok) wf = fibre_weight(a.w, p, q);
     }
     const ent* src = in + (p + a.P * (int64_t)n * q);
     for (int k0 = tid >> sh; k0 < K4; k0 += kstep * U) {
@@ -238,7 +238,7 @@ __device__ __forceinline__ void res_tile(const ResArgs& a, int64_t tile, void* l
     if constexpr (PH) {
       if (a.s_pre != 0.0) {
         st re = v[0], im = v[1];
-        if (a.winv) vortex_phase<st>(re, im, (st)(0.5 * a.s_pre), (st)(wf * a.winv[(int64_t)a.wmu * 4096 + min(k, n - 1)]));
+        if (a.w.winv) vortex_phase<st>(re, im, (st)(0.5 * a.s_pre), (st)(wf * a.w.winv[(int64_t)a.w.wmu * 4096 + min(k, n - 1)]));
         else phase<st>(re, im, (st)a.s_pre);
         v = st2{re, im};
       }
@@ -334,7 +334,7 @@ __device__ __forceinline__ void res_tile(const ResArgs& a, int64_t tile, void* l
       ent* dst = out + (p + a.P * (int64_t)a.m * q);
       double wf = 0.0;
       if constexpr (PH) {
-        if (a.winv && a.s_post != 0.0) wf = fibre_weight(a, p, q);
+        if (a.w.winv && a.s_post != 0.0) wf = fibre_weight(a.w, p, q);
       }
 #pragma unroll
       for (int i = 0; i < MF; ++i)
@@ -346,7 +346,7 @@ __device__ __forceinline__ void res_tile(const ResArgs& a, int64_t tile, void* l
             if constexpr (PH) {
               if (a.s_post != 0.0) {
                 st re = y[0], im = y[1];
-                if (a.winv) vortex_phase<st>(re, im, (st)(0.5 * a.s_post), (st)(wf * a.winv[(int64_t)a.wmu * 4096 + row]));
+                if (a.w.winv) vortex_phase<st>(re, im, (st)(0.5 * a.s_post), (st)(wf * a.w.winv[(int64_t)a.w.wmu * 4096 + row]));
                 else phase<st>(re, im, (st)a.s_post);
                 y = st2{re, im};
               }
