@@ -620,14 +620,15 @@ bool rs_plan(const ModeArgs& a, int prec, ModePlan* plan) {
 }
 
 namespace {
-// Whether the built-in choice for a complex split product is class 6: always
-// where the other classes gather unaligned fibres entry by entry (FP16X2 n = 81
-// 9.6 us against 15.7, n = 141 30 against 39-42), and up to 200 entries on
-// aligned ones (mode 2, class 6 / best other built-in choice, us: n = 48
-// 6.1 / 9.3, 64 7.0 / 9.4, 128 17.0 / 16.8, 192 60 / 73; BF16X3 64 5.3 / 9.8,
-// 192 80 / 109).  Above, its 32- and 64-fibre tiles stream the operator too
-// often (n = 224 103 / 81, 256 138 / 106).
-bool rs_rule(const ModeArgs& a, int load) { return load == KL_GENERIC || (a.Mr <= 400 && a.Kr <= 400); }
+// Whether the built-in choice for a complex split product is class 6: up to
+// 200 entries.  Unaligned fibres, which the other classes gather entry by entry
+// (FP16X2, mode 1 / 2, us, against class 0): n = 81 9.6 / 9.5 (15.7 / 15.6),
+// 141 30 / 30 (42 / 39), 181 50 / 48 (62 / 49); aligned ones (mode 2, class 6 /
+// best other built-in choice): n = 48 6.1 / 9.3, 64 7.0 / 9.4, 128 17.0 / 16.8,
+// 192 60 / 73; BF16X3 64 5.3 / 9.8, 192 80 / 109.  Above, its 32- and 64-fibre
+// tiles stream the operator too often (mode 2, n = 211 80 / 72 unaligned, 224
+// 103 / 81, 256 138 / 106).
+bool rs_rule(const ModeArgs& a) { return a.Mr <= 400 && a.Kr <= 400; }
 }  // namespace
 
 bool plan_mode(const ModeArgs& a, int prec, int cplx, bool want_pro, bool want_epi, bool fcontig_ok,
@@ -654,7 +655,7 @@ bool plan_mode(const ModeArgs& a, int prec, int cplx, bool want_pro, bool want_e
   op_blocks(prec, a.Mr, a.Kr, &kbt, &mft);
   // resident-tile split kernel (class 6): any stride, at most 256 complex
   // rows and columns
-  if (split && cplx && !batch && (force_cls == RS_CLASS || (force_cls < 0 && rs_rule(a, load))) &&
+  if (split && cplx && !batch && (force_cls == RS_CLASS || (force_cls < 0 && rs_rule(a))) &&
       rs_plan(a, prec, plan)) {
     plan->prec = prec;
     plan->cplx = cplx;

@@ -1846,6 +1846,13 @@ mm_status mm_autotune(mm_ctx ctx, const mm_tensor* T, const mm_op* E, int budget
       ctx->force_cls = -1;
       if (st == MM_OK && plan.cls == c) cands.push_back(c);
     }
+    // unaligned fibres of a split product: only the gather of class 0 and
+    // class 6 exist, and the built-in rule separates them
+    if ((kp == mm::KP_BF16X3 || kp == mm::KP_FP16X2) && cands.size() > 1) {
+      mm::ModePlan plan;
+      st = run_mode(ctx, T->data, ctx->ws, T->dims, T->d, T->dtype, L, k + 1, 0, 0, s, &plan, true);
+      if (st == MM_OK && plan.load == mm::KL_GENERIC) cands = {plan.cls};
+    }
     if (cands.empty()) continue;
     // complex products with a complex operator are timed a second time with
     // the fused prologue phase (the first product of a Gross-Pitaevskii
