@@ -25,7 +25,7 @@ __global__ __launch_bounds__(256) void res_run_kernel(ResArgs a) {
 }
 
 template <int PR>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PR == KP_F32 ? 4 : 3)))
 void res_batch_kernel(const ResArgs* __restrict__ args,
                                                         const ResItem* __restrict__ items) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -34,12 +34,16 @@ void res_batch_kernel(const ResArgs* __restrict__ args,
   switch (it.kind) {
 #define MM_RK(F_, M_) \
   case F_ * 10 + M_: res_tile<PR, F_, M_, 1, false>(a, it.tile, lds); break;
-    MM_RK(RF_C3, 1) MM_RK(RF_C3, 2) MM_RK(RF_C3, 3) MM_RK(RF_C3, 4)
+    MM_RK(RF_C3, 1) MM_RK(RF_C3, 2) MM_RK(RF_C3, 3)
 #if MM_RES_C4
-    MM_RK(RF_C4, 1) MM_RK(RF_C4, 2) MM_RK(RF_C4, 3) MM_RK(RF_C4, 4)
+    MM_RK(RF_C4, 1) MM_RK(RF_C4, 2) MM_RK(RF_C4, 3)
 #endif
-    MM_RK(RF_RC, 1) MM_RK(RF_RC, 2) MM_RK(RF_RC, 3) MM_RK(RF_RC, 4)
-    MM_RK(RF_RR, 1) MM_RK(RF_RR, 2) MM_RK(RF_RR, 3) MM_RK(RF_RR, 4)
+    MM_RK(RF_RC, 1) MM_RK(RF_RC, 2) MM_RK(RF_RC, 3)
+    MM_RK(RF_RR, 1)
+#undef MM_RK
+#define MM_RK(M_) \
+  case RES_KIND_NF2 + M_: res_tile<PR, RF_RR, M_, 2, false>(a, it.tile, lds); break;
+    MM_RK(1) MM_RK(2) MM_RK(3)
 #undef MM_RK
     default: break;
   }

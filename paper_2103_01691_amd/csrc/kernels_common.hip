@@ -561,10 +561,14 @@ void res_batch_plan(int prec, int form, ResArgs* a, int* kind, int64_t* tiles, s
   const int frags = (a->m + 15) / 16;
   a->WM = frags <= 1 ? 1 : (frags <= 2 ? 2 : 4);
   a->WN = 4 / a->WM;
-  a->NRB = (frags + 15) / 16;
+  // at most three fragments per wave (and so 128 registers in FP32, four waves
+  // per SIMD), the rows in as many passes as that takes
+  a->NRB = (frags + 11) / 12;
   const int mf = (frags + a->WM * a->NRB - 1) / (a->WM * a->NRB);
-  *kind = form * 10 + mf;
-  const int nt = 16 * a->WN;
+  // real fibres: half the operator traffic per fibre, which they would wait for
+  const int nf = form == RF_RR && frags > 2 ? 2 : 1;
+  *kind = nf == 2 ? RES_KIND_NF2 + mf : form * 10 + mf;
+  const int nt = 16 * nf * a->WN;
   *tiles = (a->F + nt - 1) / nt;
   *lds = (size_t)res_lds_rows(a->n) * (nt + 1) * (prec == KP_F64 ? 8 : 4) * (form == RF_RR ? 1 : 2);
 }

@@ -178,7 +178,9 @@ hipError_t launch_res(const ResPlan& p, const ResArgs& a, hipStream_t s, hipEven
 hipError_t launch_res_f64(const ResPlan& p, const ResArgs& a, hipStream_t s, hipEvent_t start, hipEvent_t stop);
 hipError_t launch_res_f32(const ResPlan& p, const ResArgs& a, hipStream_t s, hipEvent_t start, hipEvent_t stop);
 // Batched form: work item i runs tile `tile` of args[arg] with the tile code
-// kind = form * 10 + MF (4 waves, NF = 1); res_batch_plan fills WM, WN, NRB.
+// kind = form * 10 + MF (4 waves, NF = 1), or RES_KIND_NF2 + MF for real fibres
+// with NF = 2; res_batch_plan fills WM, WN, NRB.
+constexpr int RES_KIND_NF2 = 100;
 void res_batch_plan(int prec, int form, ResArgs* a, int* kind, int64_t* tiles, size_t* lds);
 struct ResItem {
   int arg, kind;

@@ -500,6 +500,7 @@ mm_status upload(mm_ctx ctx, V** dev, size_t* cap, const std::vector<V>& host) {
 // Relative MFMA time of one batched tile.
 int64_t res_tile_cost(const mm::ResArgs& a, int kind) {
   const int form = kind / 10, mf = kind % 10;
+  if (kind >= mm::RES_KIND_NF2) return (int64_t)a.n * mf * a.NRB * 2;
   return (int64_t)a.n * mf * a.NRB * (form == mm::RF_C4 ? 4 : (form == mm::RF_C3 ? 3 : (form == mm::RF_RC ? 2 : 1)));
 }
 

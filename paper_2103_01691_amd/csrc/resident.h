@@ -262,6 +262,7 @@ __device__ __forceinline__ void res_tile(const ResArgs& a, int64_t tile, void* l
       for (int j = 0; j < NF; ++j)
 #pragma unroll
         for (int t = 0; t < NP; ++t) acc[i][j][t] = acc_t{0, 0, 0, 0};
+    if (mf0 * 16 >= a.m) return;         // a wave past the last row only stages
     const ent* Lk = Lb;
 #pragma unroll
     for (int j = 0; j < NF; ++j) b[0][j] = Lk[16 * j];
