@@ -602,17 +602,21 @@ hipError_t launch_prepare_gauss(int prec, const double* master, int64_t rows, in
   return hipGetLastError();
 }
 
-bool rs_plan(const ModeArgs& a, int prec, ModePlan* plan) {
+bool rs_plan(const ModeArgs& a, int prec, int cplx, ModePlan* plan) {
   if (a.Mr > 512 || a.Kr > 512) return false;
   const int kb = (a.Kr + 15) / 16;
   const int npb = prec == KP_BF16X3 ? 3 : 2;
+  const int form = cplx ? RS_CC : (a.rview ? RS_RC : RS_RR);
   auto lds = [&](int nf) { return (size_t)kb * nf * npb * 1024; };
+  const bool two = lds(2) <= 160 * 1024 && (prec != KP_BF16X3 || a.Mr <= 256);
   // 64 fibres per tile, 32 where that would leave CUs without one or not fit
-  // the 160 KiB of LDS
-  const int nf = (lds(2) <= 160 * 1024 && a.F >= 64 * 200 && (prec != KP_BF16X3 || a.Mr <= 256)) ? 2 : 1;
+  // the 160 KiB of LDS; the two planes of 32 complex fibres for RC
+  const int nf = form == RS_RC ? 2 : (two && a.F >= 64 * 200 ? 2 : 1);
+  if (form == RS_RC && !two) return false;
   *plan = ModePlan{};
   plan->cls = RS_CLASS;
   plan->rs = nf;
+  plan->rs_form = form;
   plan->rs_lds = std::max<size_t>(lds(nf), 256);
   plan->nt = 32 * nf;
   plan->mt_rows = 512;
@@ -624,15 +628,24 @@ bool rs_plan(const ModeArgs& a, int prec, ModePlan* plan) {
 }
 
 namespace {
-// Whether the built-in choice for a complex split product is class 6: up to
-// 200 entries.  Unaligned fibres, which the other classes gather entry by entry
+// Whether the built-in choice for a split product is class 6: operators of up
+// to 400 real rows and columns.  Complex ones (200 entries): unaligned fibres, which the other classes gather entry by entry
 // (FP16X2, mode 1 / 2, us, against class 0): n = 81 9.6 / 9.5 (15.7 / 15.6),
 // 141 30 / 30 (42 / 39), 181 50 / 48 (62 / 49); aligned ones (mode 2, class 6 /
 // best other built-in choice): n = 48 6.1 / 9.3, 64 7.0 / 9.4, 128 17.0 / 16.8,
 // 192 60 / 73; BF16X3 64 5.3 / 9.8, 192 80 / 109.  Above, its 32- and 64-fibre
 // tiles stream the operator too often (mode 2, n = 211 80 / 72 unaligned, 224
-// 103 / 81, 256 138 / 106).
-bool rs_rule(const ModeArgs& a) { return a.Mr <= 400 && a.Kr <= 400; }
+// 103 / 81, 256 138 / 106).  Real ones (mode 1 / 2, us, class 6 against the
+// fastest other class), FP16X2 on complex fibres: n = 64 7.0 / 9.1 (9.2 / 9.1),
+// 81 9.4 / 9.8 (17.2 / 17.1), 128 15.9 / 16.1 (19.4 / 15.9), 256 74 / 83
+// (129 / 110), 400 509 / 492 (660 / 570); on real fibres 256 46 / 49 (73 / 59),
+// 400 262 / 276 (337 / 283), 500 611 / 586 (888 / 519); BF16X3 on real fibres
+// 256 69 / 77 (89 / 76), 350 273 / 276 (366 / 291), 400 444 / 436 (457 / 413):
+// there the line is at 352 rows.
+bool rs_rule(const ModeArgs& a, int prec, int cplx) {
+  const int most = !cplx && prec == KP_BF16X3 ? 352 : 400;
+  return a.Mr <= most && a.Kr <= most;
+}
 }  // namespace
 
 bool plan_mode(const ModeArgs& a, int prec, int cplx, bool want_pro, bool want_epi, bool fcontig_ok,
@@ -657,10 +670,10 @@ bool plan_mode(const ModeArgs& a, int prec, int cplx, bool want_pro, bool want_e
   // (three-product classes: their own padding, a multiple of every chunk)
   int kbt = 0, mft = 0;
   op_blocks(prec, a.Mr, a.Kr, &kbt, &mft);
-  // resident-tile split kernel (class 6): any stride, at most 256 complex
-  // rows and columns
-  if (split && cplx && !batch && (force_cls == RS_CLASS || (force_cls < 0 && rs_rule(a))) &&
-      rs_plan(a, prec, plan)) {
+  // resident-tile split kernel (class 6): any stride, at most 512 real rows
+  // and columns
+  if (split && !batch && (force_cls == RS_CLASS || (force_cls < 0 && rs_rule(a, prec, cplx))) &&
+      rs_plan(a, prec, cplx, plan)) {
     plan->prec = prec;
     plan->cplx = cplx;
     plan->load = load;

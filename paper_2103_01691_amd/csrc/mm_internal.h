@@ -64,6 +64,7 @@ struct ModeArgs {
   // epilogue adds the input entry at the same position back in FP32 (after
   // the prologue phase when there is one)
   int idadd;
+  int rview;           // real operator on the (re, im) planes of a complex state
 };
 
 // Per-workgroup work item of a batched launch.
@@ -200,15 +201,17 @@ struct ModePlan {
   int full;            // every tile complete and output offsets fit 32 bits
   int gauss;           // three-product kernel: the operator's Gauss preparation
   int rs = 0;          // resident-tile split kernel (class 6): N-fragments per tile
+  int rs_form = 0;     // RsForm
   size_t rs_lds = 0;
   int res = 0;         // resident-tile kernel (FP64 / FP32; rp is its launch shape)
   ResPlan rp;
 };
 
-// Resident-tile kernels of the complex split products (rsplit.h), tile class 6
-// of FP16X2 and BF16X3: modes of at most 256 complex entries.
+// Resident-tile kernels of the split products (rsplit.h), tile class 6 of FP16X2
+// and BF16X3: operators of at most 512 real rows and columns.
 constexpr int RS_CLASS = 6;
-bool rs_plan(const ModeArgs& a, int prec, ModePlan* plan);
+enum RsForm { RS_CC = 0, RS_RC = 1, RS_RR = 2 };   // operator x fibres: complex or real
+bool rs_plan(const ModeArgs& a, int prec, int cplx, ModePlan* plan);
 hipError_t launch_rsplit_fp16x2(const ModePlan& p, const ModeArgs& a, const VortexW& w, hipStream_t s, hipEvent_t start,
                                 hipEvent_t stop);
 hipError_t launch_rsplit_bf16x3(const ModePlan& p, const ModeArgs& a, const VortexW& w, hipStream_t s, hipEvent_t start,

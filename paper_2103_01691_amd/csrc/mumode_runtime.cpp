@@ -361,6 +361,7 @@ mm_status run_mode(mm_ctx ctx, const void* in, void* out, const int64_t* dims, i
   a.smax_clr = nullptr;
   a.a_exp = L->a_exp;
   a.idadd = L->idsplit;
+  a.rview = rview ? 1 : 0;
   const bool kcontig = (P == 1) && (a.Kr % 8 == 0);
   const bool fcontig = (P % 4 == 0);
   const bool pair = !kcontig && !cplx && P == 2 && a.Kr % 8 == 0;   // as the planner decides
@@ -1611,6 +1612,7 @@ mm_status mumode_expstep_batched(mm_ctx ctx, int count, mm_tensor* const* T, con
         a.smax_clr = nullptr;
         a.a_exp = 0;
         a.idadd = L->idsplit;
+        a.rview = 0;
         // one merged launch per (mode, precision, identity split); the item's
         // kind selects its tile code
         const uint64_t key = (uint64_t)plan.prec * 2 + (L->idsplit ? 1 : 0);
