@@ -44,7 +44,8 @@ KERNEL_SOURCES = ["paper_2103_01691_amd/csrc/mode_tile.h", "paper_2103_01691_amd
                   "paper_2103_01691_amd/csrc/kern_bf16x3_ida.hip", "paper_2103_01691_amd/csrc/kern_fp16x2_ida.hip",
                   "paper_2103_01691_amd/csrc/kernels_common.hip", "paper_2103_01691_amd/build.py",
                   "paper_2103_01691_amd/csrc/mode_gauss.h", "paper_2103_01691_amd/csrc/kern_bf16x3_g.hip",
-                  "paper_2103_01691_amd/csrc/kern_fp16x2_g.hip"]
+                  "paper_2103_01691_amd/csrc/kern_fp16x2_g.hip", "paper_2103_01691_amd/csrc/rsplit.h",
+                  "paper_2103_01691_amd/csrc/kern_rsplit.inl"]
 
 
 def kernel_source_hash():
@@ -339,7 +340,7 @@ def _heat_workload(ctx, mm, torch, gen):
     ctx.mm_set_option(mm.MM_OPT_SMALL_RUN, 1)
     out["heat64x64_fp64_20steps"] = {"calls_per_s": K / t, "us_per_step": 1e6 * t / (20 * K),
                                      "us_per_step_one_launch_per_product": 1e6 * t_per / (20 * K),
-                                     "note": "default: all 20 steps in one single-workgroup launch"}
+                                     "note": "default: all 20 steps of a mode in one launch, the operator in registers"}
     Eop.destroy()
     torch.cuda.empty_cache()
     return out

@@ -338,7 +338,9 @@ mm_status mm_autotune(mm_ctx ctx, const mm_tensor* T, const mm_op* E, int budget
  * count, T and E): for each mode and each of real / complex instances, the
  * tile class of that group's products in the merged launches (0..2, or the
  * planner's own choice) is chosen by timing whole batched steps, one group
- * at a time with the others held (coordinate descent).  Tiles that are
+ * at a time with the others held (coordinate descent); FP64 and FP32 groups
+ * of at most 256 complex / 512 real rows have one kernel and keep the
+ * planner's choice.  Tiles that are
  * fastest for an instance alone need not be fastest inside the merged
  * launch, where every instance's tiles share the GPU, so the choice is made
  * on the batch itself.  Runs the step in place on T several times (the

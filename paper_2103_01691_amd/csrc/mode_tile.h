@@ -1052,10 +1052,11 @@ template <int PR, int CLS> struct Cfg;
 template <> struct Cfg<KP_F64, 0> { static constexpr int WMF = 8, WNF = 2, WM = 4, WN = 1, KCH = 8; static constexpr int OCC = 1; };
 template <> struct Cfg<KP_F64, 1> { static constexpr int WMF = 8, WNF = 1, WM = 2, WN = 2, KCH = 8; static constexpr int OCC = 1; };
 template <> struct Cfg<KP_F64, 2> { static constexpr int WMF = 8, WNF = 1, WM = 1, WN = 4, KCH = 8; static constexpr int OCC = 1; };
+// FP64 and FP32 products of at most 256 complex / 512 real rows run on the
+// resident-tile kernels (resident.h); these classes serve the longer ones.
 // FP64 class 3: one wave, 32 real rows x 16 fibres, four waves per SIMD, for
-// products with few fibres (the 2-D matrix products of the device
-// exponential: a 256 x 256 complex product has 256 fibres, 8 workgroups of
-// class 0 but 256 of this class); it splits the rows over workgroups, so its
+// products with few fibres (the 2-D matrix products of the device exponential
+// of matrices above 256, which leave most CUs idle in class 0); it splits the rows over workgroups, so its
 // products run out of place
 template <> struct Cfg<KP_F64, 3> { static constexpr int WMF = 2, WNF = 1, WM = 1, WN = 1, KCH = 8; static constexpr int OCC = 4; };
 template <> struct Cfg<KP_F32, 0> { static constexpr int WMF = 4, WNF = 2, WM = 4, WN = 1, KCH = 32; static constexpr int OCC = 1; };

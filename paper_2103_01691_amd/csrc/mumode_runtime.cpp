@@ -61,7 +61,7 @@ struct mm_ctx_s {
   int force_cls = -1;            // set while the autotuner times a class
   std::string tune_path;         // tune cache file (mm_create), "" if none
   std::array<int64_t, 6> last_key{};   // tune key of the last planned product
-  bool small_run = true;         // whole-run single-workgroup kernel for small expsteps
+  bool small_run = true;         // several steps of a mode per launch (FP64 / FP32 expsteps)
   // in-call monitor (MM_OPT_MONITOR_EVERY): sum |T|^2 every mon_every steps
   // of mumode_expstep / gpe_strang_step, kept on the device until the call ends
   int mon_every = 0;
