@@ -1344,9 +1344,11 @@ mm_status ho_strang_step(mm_ctx ctx, mm_tensor* psi, const mm_op* Phi_fwd, const
     need[k] = (mm::prepared_bytes(L.lay, L.KBT, L.MFT) + 255) / 256 * 256;
     per_step += need[k];
   }
-  int blk = eps != 0.0 ? std::min(nsteps, 32) : 1;
+  int blk = eps != 0.0 ? 32 : 1;
   while (blk > 1 && per_step * blk > ((size_t)64 << 20)) blk /= 2;
-  blk = std::max(blk, 1);
+  // (the buffers hold a whole block from the first call on: growing them for
+  // a call of more steps costs 1 ms of waiting, freeing and allocating, as
+  // much as 17 steps at n = 128)
   for (int k = 0; k < psi->d; ++k) {
     const size_t want = need[k] * blk;
     if (ctx->step_prep_bytes[k] < want) {
