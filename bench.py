@@ -456,6 +456,8 @@ def main():
                 prec, (SPLIT_PRODUCTS.get(prec, 1), PEAK["bf16"]))
             if prec in SPLIT_PRODUCTS:
                 mult *= executed_share(ptuned)
+            else:   # the step's operator is near the identity: three real products for four
+                mult *= 0.75
             side[prec] = {"ms_per_step": pms, "steps_per_s": 1e3 / pms, "tflops_effective": eff,
                           "executed_mfma_frac_per_step": mult * eff * 1e12 / peak}
             if prec in SPLIT_PRODUCTS:
