@@ -1350,7 +1350,7 @@ mm_status ho_strang_step(mm_ctx ctx, mm_tensor* psi, const mm_op* Phi_fwd, const
   // a call of more steps costs 1 ms of waiting, freeing and allocating, as
   // much as 17 steps at n = 128)
   for (int k = 0; k < psi->d; ++k) {
-    const size_t want = need[k] * blk;
+    size_t want = need[k] * blk;
     if (ctx->step_prep_bytes[k] < want) {
       if (ctx->step_prep[k]) {
         HIPCHK(ctx, hipDeviceSynchronize());
@@ -1358,7 +1358,13 @@ mm_status ho_strang_step(mm_ctx ctx, mm_tensor* psi, const mm_op* Phi_fwd, const
         ctx->step_prep[k] = nullptr;
         ctx->step_prep_bytes[k] = 0;
       }
-      if (hipMalloc(&ctx->step_prep[k], want) != hipSuccess) return fail(ctx, MM_ERR_NOMEM, "step operators");
+      if (hipMalloc(&ctx->step_prep[k], want) != hipSuccess) {
+        // no room for a whole block: this call's steps
+        (void)hipGetLastError();
+        blk = std::min(blk, std::max(nsteps, 1));
+        want = need[k] * blk;
+        if (hipMalloc(&ctx->step_prep[k], want) != hipSuccess) return fail(ctx, MM_ERR_NOMEM, "step operators");
+      }
       ctx->step_prep_bytes[k] = want;
     }
   }
