@@ -516,10 +516,14 @@ int num_classes(int prec) {
   return (prec == KP_BF16X3 || prec == KP_FP16X2) ? 11 : ((prec == KP_F64 || prec == KP_F32) ? 4 : 3);
 }
 
-// Fragments per wave (MF) by the operator's rows: one up to 64 rows (four
-// waves already share the tile), two up to 256 (at most eight waves, 128
-// registers or fewer, so four waves fit each SIMD), four above (real
-// operators of up to 512 rows).  Short operators put several 16-fibre groups
+// Fragments per wave (MF) by the operator's rows: one up to 80 rows (four or
+// five waves share the tile; two would make an odd fifth fragment a whole
+// padded one: us, modes 1 / 2 of n = 72, one against two, FP64 complex 9.9 /
+// 10.2 against 12.3 / 11.4, FP32 7.7 / 7.9 against 9.1 / 8.6, real 4.7 / 4.9
+// against 5.4 / 5.1), two or three up to 256 (at most eight waves, 128
+// registers or fewer, so four waves fit each SIMD; three where it divides the
+// nine to twelve fragments: FP64 n = 168 102 / 98 against 132 / 132), four
+// above (real operators of up to 512 rows).  Short operators put several 16-fibre groups
 // in one workgroup, unless that would leave fewer than two workgroups per CU.
 void res_plan(int prec, int form, bool ph, int cls, ResArgs* a, ResPlan* p) {
   const int frags = (a->m + 15) / 16;
@@ -539,7 +543,7 @@ void res_plan(int prec, int form, bool ph, int cls, ResArgs* a, ResPlan* p) {
     return;
   }
   int mf = cls >= 0 ? std::min(cls, 3) + 1
-                    : (frags <= 4 ? 1 : (frags <= 8 ? 2 : (frags <= 12 ? 3 : (frags <= 16 ? 2 : 4))));
+                    : (frags <= 5 ? 1 : (frags <= 8 ? 2 : (frags <= 12 ? 3 : (frags <= 16 ? 2 : 4))));
   while (mf < 4 && (frags + mf - 1) / mf > (mf == 1 ? 16 : 8)) ++mf;
   p->prec = prec;
   p->form = form;

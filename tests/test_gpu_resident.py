@@ -14,7 +14,7 @@ from oracle import schemes as sc
 pytestmark = pytest.mark.gpu
 
 # (n, m): fragment edges, the largest complex / real sides, rectangles
-COMPLEX = [(1, 1), (3, 16), (16, 17), (31, 64), (64, 65), (81, 81), (129, 128), (141, 145), (192, 193), (256, 256)]
+COMPLEX = [(1, 1), (3, 16), (16, 17), (31, 64), (64, 65), (80, 80), (81, 81), (129, 128), (141, 145), (192, 193), (256, 256)]
 REAL = COMPLEX + [(257, 300), (512, 512)]
 
 
