@@ -194,7 +194,7 @@ mm_status gpe_strang_step(mm_ctx ctx, mm_tensor* psi, const mm_op* E, double tau
  * the same computation and kernels, bit for bit, with no hipMalloc, hipFree
  * or other allocating call.  The device memory the split FP16X2 products need
  * besides psi (the running-bound slots and the max-abs partial maxima,
- * 4192 bytes) is a fixed array in the library that each GPU holds until the
+ * 10240 bytes) is a fixed array in the library that each GPU holds until the
  * process ends; every call on one GPU shares it (each call's first product
  * rewrites all of it), so calls that overlap on one GPU, from any context or
  * stream, race.  Limits: every n_mu <= 256 (each product runs in place, no

@@ -333,7 +333,7 @@ __global__ __launch_bounds__(NORM_THREADS) void maxabs_final_kernel(const uint32
     __syncthreads();
   }
   // slot 0 gets the bound (word 0; its other words and slots 1, 2 cleared)
-  for (int i = threadIdx.x; i < 3 * SMAX_WORDS; i += NORM_THREADS) slots[i] = i == 0 ? red[0] : 0u;
+  for (int i = threadIdx.x; i < 3 * SMAX_WORDS; i += NORM_THREADS) slots[i * SMAX_STRIDE] = i == 0 ? red[0] : 0u;
 }
 
 // ------------------------------------------------------ device expm ------

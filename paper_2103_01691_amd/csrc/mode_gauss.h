@@ -91,9 +91,9 @@ __device__ __forceinline__ void gauss_tile(const ModeArgs& a, int64_t tile_x, in
   if constexpr (F16) {
     uint32_t bbits = 0;
 #pragma unroll
-    for (int w = 0; w < SMAX_WORDS; ++w) bbits = max(bbits, a.smax_in[w]);
+    for (int w = 0; w < SMAX_WORDS; ++w) bbits = max(bbits, a.smax_in[w * SMAX_STRIDE]);
     s_exp = fp16x2_state_exp(bbits) + 1;
-    if (tile_x == 0 && tile_y == 0 && tid < SMAX_WORDS) a.smax_clr[tid] = 0u;
+    if (tile_x == 0 && tile_y == 0 && tid < SMAX_WORDS) a.smax_clr[tid * SMAX_STRIDE] = 0u;
     const float bnd = __uint_as_float(bbits);
     ph_small = fabsf((float)a.s_pre) * 2.0f * bnd * bnd <= 0.78f;
   }
@@ -410,7 +410,7 @@ __device__ __forceinline__ void gauss_tile(const ModeArgs& a, int64_t tile_x, in
       uint32_t m = 0;
 #pragma unroll
       for (int w = 0; w < WM; ++w) m = max(m, wmx[w]);
-      atomicMax(a.smax_out + (int)(tile_x % SMAX_WORDS), m);
+      atomicMax(a.smax_out + (int)(tile_x % SMAX_WORDS) * SMAX_STRIDE, m);
     }
   }
 }

@@ -297,9 +297,9 @@ __device__ __forceinline__ void mode_tile(const ModeArgs& a, int64_t tile_x, int
   if constexpr (F16) {
     uint32_t bbits = 0;
 #pragma unroll
-    for (int w = 0; w < SMAX_WORDS; ++w) bbits = max(bbits, a.smax_in[w]);
+    for (int w = 0; w < SMAX_WORDS; ++w) bbits = max(bbits, a.smax_in[w * SMAX_STRIDE]);
     s_exp = fp16x2_state_exp(bbits);
-    if (tile_x == 0 && tile_y == 0 && tid < SMAX_WORDS) a.smax_clr[tid] = 0u;
+    if (tile_x == 0 && tile_y == 0 && tid < SMAX_WORDS) a.smax_clr[tid * SMAX_STRIDE] = 0u;
     const float bnd = __uint_as_float(bbits);
     ph_small = fabsf((float)a.s_pre) * 2.0f * bnd * bnd <= 0.78f;
   }
@@ -1018,7 +1018,7 @@ __device__ __forceinline__ void mode_tile(const ModeArgs& a, int64_t tile_x, int
       uint32_t m = 0;
 #pragma unroll
       for (int w = 0; w < WM * WN; ++w) m = max(m, wmx[w]);
-      atomicMax(a.smax_out + (int)(tile_x % SMAX_WORDS), m);
+      atomicMax(a.smax_out + (int)(tile_x % SMAX_WORDS) * SMAX_STRIDE, m);
     }
   }
 }

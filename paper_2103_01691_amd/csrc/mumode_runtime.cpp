@@ -18,11 +18,11 @@
 #include "mm_internal.h"
 
 // Device memory of gpe_strang_step_noalloc: the FP16X2 running-bound slots
-// (3 x SMAX_WORDS words) and the max-abs pass's partial maxima, in a
+// (3 x SMAX_SLOT words) and the max-abs pass's partial maxima, in a
 // file-scope array each GPU holds for the life of the process, so that call
 // allocates nothing.  Host code never uses the array's name as an address:
 // the device address comes from hipGetSymbolAddress, once per device.
-constexpr int NOALLOC_SCRATCH_WORDS = 3 * mm::SMAX_WORDS + 1024;
+constexpr int NOALLOC_SCRATCH_WORDS = 3 * mm::SMAX_SLOT + 1024;
 static __device__ __align__(256) uint32_t scratch[NOALLOC_SCRATCH_WORDS];
 
 struct mm_op_s {
@@ -77,7 +77,7 @@ struct mm_ctx_s {
   double* host_result = nullptr; // pinned
   // FP16X2 state bounds: three slots of SMAX_WORDS words rotate along a
   // chain of products (launch k reads slot k % 3, raises (k + 1) % 3,
-  // clears (k + 2) % 3); words [3 SMAX_WORDS, + norm_partials()) are the
+  // clears (k + 2) % 3); words [3 SMAX_SLOT, + norm_partials()) are the
   // max-abs pass's partial maxima.  chain_end is the
   // output of the chain's last launch: a product whose input is anything
   // else (or the first one of an API call) starts a new chain with a
@@ -452,12 +452,12 @@ mm_status run_mode(mm_ctx ctx, const void* in, void* out, const int64_t* dims, i
     if (in != ctx->chain_end) {
       int64_t count = is_complex(dt) ? 2 : 1;
       for (int k = 0; k < d; ++k) count *= dims[k];
-      HIPCHK(ctx, mm::launch_maxabs((const float*)in, count, ctx->smax + 3 * mm::SMAX_WORDS, ctx->smax, s));
+      HIPCHK(ctx, mm::launch_maxabs((const float*)in, count, ctx->smax + 3 * mm::SMAX_SLOT, ctx->smax, s));
       ctx->sidx = 0;
     }
-    a.smax_in = ctx->smax + mm::SMAX_WORDS * ctx->sidx;
-    a.smax_out = ctx->smax + mm::SMAX_WORDS * ((ctx->sidx + 1) % 3);
-    a.smax_clr = ctx->smax + mm::SMAX_WORDS * ((ctx->sidx + 2) % 3);
+    a.smax_in = ctx->smax + mm::SMAX_SLOT * ctx->sidx;
+    a.smax_out = ctx->smax + mm::SMAX_SLOT * ((ctx->sidx + 1) % 3);
+    a.smax_clr = ctx->smax + mm::SMAX_SLOT * ((ctx->sidx + 2) % 3);
     ctx->sidx = (ctx->sidx + 1) % 3;
     ctx->chain_end = out;
   }
@@ -817,7 +817,7 @@ mm_status mm_create(mm_ctx* out, int device, const char* tune_cache_path) {
   c->device = device;
   if (hipMalloc((void**)&c->red_partial, sizeof(double) * mm::norm_partials()) != hipSuccess ||
       hipMalloc((void**)&c->red_result, sizeof(double) * 4) != hipSuccess ||
-      hipMalloc((void**)&c->smax, sizeof(uint32_t) * (3 * mm::SMAX_WORDS + mm::norm_partials())) != hipSuccess ||
+      hipMalloc((void**)&c->smax, sizeof(uint32_t) * (3 * mm::SMAX_SLOT + mm::norm_partials())) != hipSuccess ||
       hipHostMalloc((void**)&c->host_result, sizeof(double) * 4, hipHostMallocDefault) != hipSuccess) {
     delete c;
     return fail(nullptr, MM_ERR_NOMEM, "context buffers");
@@ -1241,7 +1241,7 @@ mm_status gpe_strang_step(mm_ctx ctx, mm_tensor* psi, const mm_op* E, double tau
 mm_status gpe_strang_step_noalloc(mm_ctx ctx, mm_tensor* psi, const mm_op* E, double tau, double beta, int nsteps,
                                   mm_stream stream) {
   if (!ctx) return MM_ERR_ARG;
-  if (3 * mm::SMAX_WORDS + mm::norm_partials() > NOALLOC_SCRATCH_WORDS)
+  if (3 * mm::SMAX_SLOT + mm::norm_partials() > NOALLOC_SCRATCH_WORDS)
     return fail(ctx, MM_ERR_UNSUPPORTED, "scratch array smaller than the FP16X2 bound slots and partials");
   // the running-bound slots and max-abs partials of the FP16X2 products come
   // from `scratch` (every chain starts with the max-abs pass, which writes

@@ -62,9 +62,9 @@ __device__ __forceinline__ void rsplit_tile(const ModeArgs& a, const VortexW& vw
   if constexpr (F16) {
     uint32_t bits = 0;
 #pragma unroll
-    for (int w = 0; w < SMAX_WORDS; ++w) bits = max(bits, a.smax_in[w]);
+    for (int w = 0; w < SMAX_WORDS; ++w) bits = max(bits, a.smax_in[w * SMAX_STRIDE]);
     s_exp = fp16x2_state_exp(bits);
-    if (tile == 0 && tid < SMAX_WORDS) a.smax_clr[tid] = 0u;
+    if (tile == 0 && tid < SMAX_WORDS) a.smax_clr[tid * SMAX_STRIDE] = 0u;
   }
 
   // operator fragments of K-block kb for this wave
@@ -316,7 +316,7 @@ __device__ __forceinline__ void rsplit_tile(const ModeArgs& a, const VortexW& vw
     if (tid == 0) {
       uint32_t m = 0;
       for (int w = 0; w < nthr / 64; ++w) m = max(m, wmx[w]);
-      atomicMax(a.smax_out + (int)(tile % SMAX_WORDS), m);
+      atomicMax(a.smax_out + (int)(tile % SMAX_WORDS) * SMAX_STRIDE, m);
     }
   }
 }
