@@ -56,9 +56,9 @@ struct ModeArgs {
   int KBT, MFT;        // padded K-blocks and M-fragments of the prepared operator
   double s_pre;        // prologue phase: psi *= exp(-i s_pre |psi|^2) (0: off)
   double s_post;       // epilogue phase, same form
-  // FP16X2 only: running bound of the state.  Each slot is SMAX_WORDS words
-  // SMAX_STRIDE apart; the maximum over smax_in's words is the float bits of max |component| of
-  // `in`; the launch raises smax_out (workgroup tile_x into word
+  // FP16X2 only: running bound of the state.  Each slot is SMAX_WORDS words,
+  // SMAX_STRIDE apart; their maximum in smax_in is the float bits of max
+  // |component| of `in`; the launch raises smax_out (workgroup tile_x the word
   // tile_x % SMAX_WORDS) to that of `out` and clears smax_clr (the slot the
   // launch before it read).  The operator pieces represent L * 2^-a_exp.
   const uint32_t* smax_in;
