@@ -178,6 +178,8 @@ mm_status fail(mm_ctx ctx, mm_status st, const char* fmt, ...) {
   va_end(ap);
   if (ctx) ctx->err = buf;
   else g_create_err = buf;
+  // (a failed allocation's error is reported here, not by the next launch)
+  if (st == MM_ERR_NOMEM) (void)hipGetLastError();
   return st;
 }
 
@@ -1659,21 +1661,15 @@ mm_status mumode_expstep_batched(mm_ctx ctx, int count, mm_tensor* const* T, con
       }
     }
     HIPCHK(ctx, hipStreamSynchronize(s));
+    // the captured step reads the lists that the uploads overwrite or free: it
+    // goes first, so that no later call can match a rebuild that failed
+    batch_invalidate(ctx);
     if ((st = upload(ctx, &ctx->bitems, &ctx->bitems_cap, items)) != MM_OK ||
         (st = upload(ctx, &ctx->rargs, &ctx->rargs_cap, rargs)) != MM_OK ||
         (st = upload(ctx, &ctx->ritems, &ctx->ritems_cap, ritems)) != MM_OK)
       return st;
     ctx->bgroups = groups;
     // capture one step (all modes, all groups) as a graph
-    if (ctx->bexec) {
-      HIPCHK(ctx, hipGraphExecDestroy(ctx->bexec));
-      ctx->bexec = nullptr;
-    }
-    if (ctx->bgraph) {
-      HIPCHK(ctx, hipGraphDestroy(ctx->bgraph));
-      ctx->bgraph = nullptr;
-    }
-    ctx->bsig.clear();
     if (!ctx->cap_stream) HIPCHK(ctx, hipStreamCreateWithFlags(&ctx->cap_stream, hipStreamNonBlocking));
     HIPCHK(ctx, hipStreamBeginCapture(ctx->cap_stream, hipStreamCaptureModeThreadLocal));
     hipError_t le = hipSuccess;

@@ -1,0 +1,208 @@
+// The library's host side on a machine without a GPU: this program defines the
+// HIP runtime calls that libmumode.so makes (an executable's symbols come
+// before those of the libraries it loads), with device memory as host memory
+// under a budget and kernels that do nothing, and runs one scenario, named by
+// its first argument.  Launches are refused where the hardware refuses them:
+// more LDS than a workgroup has, 2^32 threads along a grid dimension.  A
+// failed expectation is printed and makes the exit status 1.
+#include <hip/hip_runtime.h>
+
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <set>
+#include <string>
+#include <vector>
+
+#include "mm_internal.h"
+#include "mumode.h"
+
+namespace {
+
+struct {
+  size_t budget = (size_t)1 << 40, used = 0;
+  long fail_at = -1;                 // index of the hipMalloc that fails from here on (-1: none)
+  long mallocs = 0, frees = 0, launches = 0;
+  hipError_t last = hipSuccess;      // what hipGetLastError reports once
+  std::map<void*, size_t> live;
+  std::map<const void*, int> max_lds;
+  long next_graph = 1;
+  std::set<long> execs;              // instantiated graphs
+  std::vector<long> graph_launches;  // graphs launched, in order
+} rt;
+
+int g_failed = 0;
+#define EXPECT(cond, ...)                          \
+  do {                                             \
+    if (!(cond)) {                                 \
+      if (++g_failed <= 20) {                      \
+        printf("%s:%d: %s: ", __FILE__, __LINE__, #cond); \
+        printf(__VA_ARGS__);                       \
+        printf("\n");                              \
+      }                                            \
+    }                                              \
+  } while (0)
+
+hipError_t check_launch(const void* fn, dim3 grid, dim3 block, size_t lds) {
+  ++rt.launches;
+  const size_t allowed = rt.max_lds.count(fn) ? (size_t)rt.max_lds[fn] : 65536;
+  if (lds > allowed || block.x * block.y * block.z > 1024 || grid.x == 0 || grid.y == 0 || grid.z == 0)
+    return rt.last = hipErrorInvalidValue;
+  if ((uint64_t)grid.x * block.x >> 32 || (uint64_t)grid.y * block.y >> 32 || (uint64_t)grid.z * block.z >> 32)
+    return rt.last = hipErrorInvalidConfiguration;
+  return hipSuccess;
+}
+
+}  // namespace
+
+extern "C" {
+hipError_t hipGetDeviceCount(int* n) { *n = 1; return hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600* p, int) {
+  std::memset(p, 0, sizeof *p);
+  std::strcpy(p->gcnArchName, "gfx950");
+  return hipSuccess;
+}
+hipError_t hipMalloc(void** p, size_t bytes) {
+  const long i = rt.mallocs++;
+  if ((rt.fail_at >= 0 && i >= rt.fail_at) || rt.used + bytes > rt.budget) return rt.last = hipErrorOutOfMemory;
+  *p = std::aligned_alloc(256, (bytes + 255) / 256 * 256);
+  rt.live[*p] = bytes;
+  rt.used += bytes;
+  return hipSuccess;
+}
+hipError_t hipFree(void* p) {
+  ++rt.frees;
+  if (!rt.live.count(p)) return hipErrorInvalidValue;
+  rt.used -= rt.live[p];
+  rt.live.erase(p);
+  std::free(p);
+  return hipSuccess;
+}
+hipError_t hipHostMalloc(void** p, size_t bytes, unsigned) { *p = std::calloc(1, bytes); return hipSuccess; }
+hipError_t hipHostFree(void* p) { std::free(p); return hipSuccess; }
+hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { std::memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) {
+  std::memcpy(d, s, n);
+  return hipSuccess;
+}
+hipError_t hipGetSymbolAddress(void** p, const void*) {
+  static char scratch[65536];
+  *p = scratch;
+  return hipSuccess;
+}
+hipError_t hipDeviceSynchronize() { return hipSuccess; }
+hipError_t hipGetLastError() {
+  const hipError_t e = rt.last;
+  rt.last = hipSuccess;
+  return e;
+}
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = (hipStream_t)0x10; return hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t* e) { *e = (hipEvent_t)0x20; return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = (hipEvent_t)0x20; return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 1.0f; return hipSuccess; }
+hipError_t hipFuncSetAttribute(const void* fn, hipFuncAttribute, int bytes) {
+  if (bytes > 160 * 1024) return hipErrorInvalidValue;
+  rt.max_lds[fn] = bytes;
+  return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void* fn, dim3 grid, dim3 block, void**, size_t lds, hipStream_t) {
+  return check_launch(fn, grid, block, lds);
+}
+hipError_t hipExtLaunchKernel(const void* fn, dim3 grid, dim3 block, void**, size_t lds, hipStream_t, hipEvent_t,
+                              hipEvent_t, int) {
+  return check_launch(fn, grid, block, lds);
+}
+hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return hipSuccess; }
+hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t* g) {
+  *g = (hipGraph_t)(uintptr_t)rt.next_graph++;
+  return hipSuccess;
+}
+hipError_t hipGraphInstantiate(hipGraphExec_t* e, hipGraph_t g, hipGraphNode_t*, char*, size_t) {
+  *e = (hipGraphExec_t)g;
+  rt.execs.insert((long)(uintptr_t)g);
+  return hipSuccess;
+}
+hipError_t hipGraphLaunch(hipGraphExec_t e, hipStream_t) {
+  if (!rt.execs.count((long)(uintptr_t)e)) return hipErrorInvalidValue;
+  rt.graph_launches.push_back((long)(uintptr_t)e);
+  return hipSuccess;
+}
+hipError_t hipGraphExecDestroy(hipGraphExec_t e) { rt.execs.erase((long)(uintptr_t)e); return hipSuccess; }
+hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
+}
+
+namespace {
+
+mm_ctx open_ctx() {
+  mm_ctx c = nullptr;
+  EXPECT(mm_create(&c, 0, nullptr) == MM_OK, "%s", mm_last_error(nullptr));
+  return c;
+}
+
+// Operator with pseudo-random entries of size 1 / cols.
+mm_op make_op(mm_ctx c, int64_t rows, int64_t cols, bool cplx, mm_prec prec) {
+  std::vector<double> v((size_t)rows * cols * (cplx ? 2 : 1));
+  uint32_t x = 12345;
+  for (double& e : v) e = ((int32_t)(x = x * 1664525u + 1013904223u)) / 2147483648.0 / (double)cols;
+  mm_matrix m = {rows, cols, rows, cplx ? MM_C128 : MM_R64, v.data(), 0};
+  mm_op op = nullptr;
+  EXPECT(mm_op_prepare(c, &m, prec, &op) == MM_OK, "%s", mm_last_error(c));
+  return op;
+}
+
+// A tensor at an address that nothing here reads (the kernels do nothing).
+mm_tensor tensor(std::vector<int64_t> dims, mm_dtype dt, uintptr_t at = (uintptr_t)1 << 40) {
+  mm_tensor T = {};
+  T.d = (int)dims.size();
+  for (int k = 0; k < T.d; ++k) T.dims[k] = dims[k];
+  T.dtype = dt;
+  T.data = (void*)at;
+  return T;
+}
+
+// A rebuild of the batched step that fails part way leaves no captured graph
+// behind: its work items may be freed or overwritten by then.
+void batch_failed_rebuild() {
+  for (int at = 0; at < 3; ++at) {
+    mm_ctx c = open_ctx();
+    mm_tensor A = tensor({16, 16}, MM_R32), B1 = tensor({64, 512, 16}, MM_R32, (uintptr_t)2 << 40),
+              B2 = tensor({64, 512, 16}, MM_R32, (uintptr_t)3 << 40), B3 = tensor({64, 64}, MM_R32, (uintptr_t)4 << 40);
+    mm_op a = make_op(c, 16, 16, false, MM_PREC_FP32), b = make_op(c, 64, 64, false, MM_PREC_FP32),
+          s = make_op(c, 64, 64, false, MM_PREC_SPLIT_BF16X3), as = make_op(c, 16, 16, false, MM_PREC_SPLIT_BF16X3);
+    mm_op Ea[MM_MAXD] = {a, as}, Eb[MM_MAXD] = {b}, Es[MM_MAXD] = {s, s};
+    mm_tensor* Ta[1] = {&A};
+    const mm_op* Eas[1] = {Ea};
+    mm_tensor* Tb[3] = {&B1, &B2, &B3};
+    const mm_op* Ebs[3] = {Eb, Eb, Es};
+    EXPECT(mumode_expstep_batched(c, 1, Ta, Eas, 1, nullptr) == MM_OK, "%s", mm_last_error(c));
+    rt.fail_at = rt.mallocs + at;    // the at-th list that has to grow
+    EXPECT(mumode_expstep_batched(c, 3, Tb, Ebs, 1, nullptr) == MM_ERR_NOMEM, "upload %d", at);
+    rt.fail_at = -1;
+    const size_t before = rt.graph_launches.size();
+    const long built = rt.next_graph;
+    EXPECT(mumode_expstep_batched(c, 1, Ta, Eas, 1, nullptr) == MM_OK, "%s", mm_last_error(c));
+    EXPECT(rt.graph_launches.size() == before + 1 && rt.graph_launches.back() >= built,
+           "graph %ld captured before the failed rebuild (upload %d)", rt.graph_launches.back(), at);
+    mm_destroy(c);
+  }
+}
+
+}  // namespace
+
+int main(int argc, char** argv) {
+  const std::map<std::string, void (*)()> scenarios = {
+      {"batch_failed_rebuild", batch_failed_rebuild},
+  };
+  const auto it = scenarios.find(argc > 1 ? argv[1] : "");
+  if (it == scenarios.end()) return 2;
+  it->second();
+  if (g_failed) printf("%d expectations failed\n", g_failed);
+  return g_failed ? 1 : 0;
+}
