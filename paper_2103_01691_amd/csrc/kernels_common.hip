@@ -554,10 +554,14 @@ void res_plan(int prec, int form, bool ph, int cls, ResArgs* a, ResPlan* p) {
   p->nf = (form == RF_RR && a->n <= 256 && a->F >= 16384) ? 2 : 1;
   while (a->WN > 1 && (a->F + 16 * p->nf * a->WN - 1) / (16 * p->nf * a->WN) < 512) a->WN /= 2;
   a->NRB = 1;
+  // an operator of few rows and long columns: the tile holds the columns
+  auto lds = [&]() { return (size_t)res_lds_rows(a->n) * (16 * p->nf * a->WN + 1) * es; };
+  while (a->WN > 1 && lds() > MAX_LDS) a->WN /= 2;
+  if (lds() > MAX_LDS) p->nf = 1;
   const int nt = 16 * p->nf * a->WN;
   p->threads = 64 * a->WM * a->WN;
   p->grid_x = (int)((a->F + nt - 1) / nt);
-  p->lds = (size_t)res_lds_rows(a->n) * (nt + 1) * es;
+  p->lds = lds();
 }
 
 // Four waves for every item of a batch: WM of them along the rows.
@@ -612,7 +616,7 @@ bool rs_plan(const ModeArgs& a, int prec, int cplx, ModePlan* plan) {
   const int npb = prec == KP_BF16X3 ? 3 : 2;
   const int form = cplx ? RS_CC : (a.rview ? RS_RC : RS_RR);
   auto lds = [&](int nf) { return (size_t)kb * nf * npb * 1024; };
-  const bool two = lds(2) <= 160 * 1024 && (prec != KP_BF16X3 || a.Mr <= 256);
+  const bool two = lds(2) <= MAX_LDS && (prec != KP_BF16X3 || a.Mr <= 256);
   // 64 fibres per tile, 32 where that would leave CUs without one or not fit
   // the 160 KiB of LDS; the two planes of 32 complex fibres for RC
   const int nf = form == RS_RC ? 2 : (two && a.F >= 64 * 200 ? 2 : 1);

@@ -169,6 +169,8 @@ inline bool res_fits(int64_t rows, int64_t cols, int cplx) {
   const int64_t lim = cplx ? 256 : 512;
   return rows <= lim && cols <= lim;
 }
+// LDS of a workgroup.
+constexpr size_t MAX_LDS = 160 * 1024;
 // LDS rows of a tile: whole operator units and one K-block that is read ahead.
 inline int res_lds_rows(int n) { return (n + 15) / 16 * 16 + 4; }
 struct ResPlan {

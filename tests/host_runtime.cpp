@@ -194,11 +194,83 @@ void batch_failed_rebuild() {
   }
 }
 
+// Launch shapes of the resident-tile products over all rows, columns and forms
+// that they take, for few to very many fibres and every forced tile class.
+template <typename Check>
+void for_all_plans(Check&& check) {
+  const int64_t fibres[] = {1, 100, 8191, 16384, 40000, 65537, (int64_t)1 << 30};
+  for (int prec : {(int)mm::KP_F64, (int)mm::KP_F32})
+    for (int form : {(int)mm::RF_C3, (int)mm::RF_RC, (int)mm::RF_RR, (int)mm::RF_C4}) {
+      if (form == mm::RF_C4 && prec == mm::KP_F64) continue;
+      const int lim = form == mm::RF_C3 || form == mm::RF_C4 ? 256 : 512;
+      for (int m = 1; m <= lim; ++m)
+        for (int n = 1; n <= lim; n += n < 64 ? 1 : 3)
+          for (int64_t F : fibres)
+            for (int cls = -1; cls < 4; ++cls) {
+              mm::ResArgs a = {};
+              a.n = n;
+              a.m = m;
+              a.P = 1;
+              a.F = F;
+              a.nsteps = 1;
+              mm::ResPlan p = {};
+              mm::res_plan(prec, form, false, cls, &a, &p);
+              check(a, p);
+              if (m == n) {
+                a.nsteps = 5;
+                mm::res_plan(prec, form, false, cls, &a, &p);
+                check(a, p);
+              }
+            }
+    }
+}
+
+void resident_plans_fit() {
+  for_all_plans([](const mm::ResArgs& a, const mm::ResPlan& p) {
+    const char* what = "prec %d form %d m %d n %d F %lld: lds %zu threads %d MF %d NF %d WM %d WN %d";
+#define WHAT what, p.prec, p.form, a.m, a.n, (long long)a.F, p.lds, p.threads, p.mf, p.nf, a.WM, a.WN
+    const size_t es = (p.prec == mm::KP_F64 ? 8 : 4) * (p.form == mm::RF_RR ? 1 : 2);
+    const int nt = 16 * p.nf * a.WN;
+    EXPECT(p.lds <= 160 * 1024, WHAT);
+    EXPECT(p.threads == 64 * a.WM * a.WN && p.threads <= (p.run ? 256 : (p.mf == 1 ? 1024 : 512)), WHAT);
+    if (p.run) EXPECT(p.lds == 2 * p.run * 17 * es && a.n <= p.run && a.WM * 16 >= a.m, WHAT);
+    else EXPECT(p.lds >= (size_t)(a.n + 4) * (nt + 1) * es && a.WM * p.mf * 16 * a.NRB >= a.m, WHAT);
+    EXPECT(p.mf >= 1 && p.mf <= 4 && (p.nf == 1 || (p.nf == 2 && p.form == mm::RF_RR)), WHAT);
+    EXPECT((int64_t)p.grid_x * nt >= a.F && (int64_t)(p.grid_x - 1) * nt < a.F, WHAT);
+  });
+}
+
+// Flat operators through the public calls, at the sizes of real transforms.
+void flat_operators() {
+  struct { int64_t m, n; bool cplx; mm_dtype dt; mm_prec prec; } cases[] = {
+      {16, 200, false, MM_C128, MM_PREC_FP64}, {16, 256, true, MM_C128, MM_PREC_FP64},
+      {16, 256, false, MM_R64, MM_PREC_FP64},  {32, 512, false, MM_C128, MM_PREC_FP64},
+      {16, 512, false, MM_C64, MM_PREC_FP32},  {1, 145, true, MM_C128, MM_PREC_FP64}};
+  mm_ctx c = open_ctx();
+  for (const auto& t : cases) {
+    mm_op L = make_op(c, t.m, t.n, t.cplx, t.prec);
+    for (int mu = 1; mu <= 2; ++mu) {
+      const std::vector<int64_t> in = mu == 1 ? std::vector<int64_t>{t.n, 256, 300} : std::vector<int64_t>{300, t.n, 256};
+      std::vector<int64_t> out = in;
+      out[mu - 1] = t.m;
+      mm_tensor T = tensor(in, t.dt), O = tensor(out, t.dt, (uintptr_t)2 << 40);
+      EXPECT(mumode_apply(c, &O, &T, L, mu, nullptr) == MM_OK, "%lld x %lld mode %d: %s", (long long)t.m,
+             (long long)t.n, mu, mm_last_error(c));
+      mm_op Phi[MM_MAXD] = {mu == 1 ? L : nullptr, mu == 2 ? L : nullptr};
+      EXPECT(mumode_transform(c, &O, &T, Phi, nullptr) == MM_OK, "%s", mm_last_error(c));
+      EXPECT(mm_autotune(c, &T, Phi, 1, nullptr) == MM_OK, "%s", mm_last_error(c));
+    }
+  }
+  mm_destroy(c);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> scenarios = {
       {"batch_failed_rebuild", batch_failed_rebuild},
+      {"resident_plans_fit", resident_plans_fit},
+      {"flat_operators", flat_operators},
   };
   const auto it = scenarios.find(argc > 1 ? argv[1] : "");
   if (it == scenarios.end()) return 2;
