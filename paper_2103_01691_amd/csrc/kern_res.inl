@@ -3,10 +3,14 @@
 // the precision has the four-product form (FP32).
 #include <hip/hip_ext.h>
 
+#include <algorithm>
+
 #include "resident.h"
 
 namespace mm {
 namespace {
+
+__device__ __forceinline__ int64_t res_block() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
 
 // Register budgets: MF <= 2 runs four waves per SIMD (at most 128 registers),
 // MF = 3, 4 two.  MF = 1 allows sixteen waves per workgroup (256 complex
@@ -15,13 +19,13 @@ template <int PR, int FORM, int MF, int NF, bool PH>
 __global__ __launch_bounds__(MF == 1 ? 1024 : 512)
 void res_kernel(ResArgs a) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
-  res_tile<PR, FORM, MF, NF, PH>(a, blockIdx.x, lds);
+  res_tile<PR, FORM, MF, NF, PH>(a, res_block(), lds);
 }
 
 template <int PR, int FORM, int KR>
 __global__ __launch_bounds__(256) void res_run_kernel(ResArgs a) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
-  res_run_tile<PR, FORM, KR>(a, blockIdx.x, lds);
+  res_run_tile<PR, FORM, KR>(a, res_block(), lds);
 }
 
 template <int PR>
@@ -92,7 +96,7 @@ hipError_t res_launch(const ResPlan& p, const ResArgs& a, hipStream_t s, hipEven
     const hipError_t e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds);
     if (e != hipSuccess) return e;
   }
-  const dim3 grid(p.grid_x), block(p.threads);
+  const dim3 grid(p.grid_x, p.grid_y), block(p.threads);
   if (start || stop) hipExtLaunchKernelGGL(fn, grid, block, p.lds, s, start, stop, 0, a);
   else hipLaunchKernelGGL(fn, grid, block, p.lds, s, a);
   return hipGetLastError();
@@ -106,8 +110,13 @@ hipError_t res_batch_launch(const ResArgs* args, const ResItem* items, int count
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(res_batch_kernel<PR>, dim3(count), dim3(256), lds, s, args, items);
-  return hipGetLastError();
+  // (fewer than 2^32 threads per launch)
+  for (int at = 0; at < count; at += 1 << 23) {
+    hipLaunchKernelGGL(res_batch_kernel<PR>, dim3(std::min(count - at, 1 << 23)), dim3(256), lds, s, args, items + at);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace

@@ -516,6 +516,14 @@ int num_classes(int prec) {
   return (prec == KP_BF16X3 || prec == KP_FP16X2) ? 11 : ((prec == KP_F64 || prec == KP_F32) ? 4 : 3);
 }
 
+// A launch takes fewer than 2^32 threads along x, which tiles of 16 fibres reach
+// on states that fit the memory (33 complex rows: 3.6e8 fibres, 94 GB in FP32).
+static void res_grid(int64_t tiles, ResPlan* p) {
+  const int64_t most = 0xffffffffll / p->threads;
+  p->grid_y = (int)((tiles + most - 1) / most);
+  p->grid_x = (int)((tiles + p->grid_y - 1) / p->grid_y);
+}
+
 // Fragments per wave (MF) by the operator's rows: one up to 80 rows (four or
 // five waves share the tile; two would make an odd fifth fragment a whole
 // padded one: us, modes 1 / 2 of n = 72, one against two, FP64 complex 9.9 /
@@ -538,7 +546,7 @@ void res_plan(int prec, int form, bool ph, int cls, ResArgs* a, ResPlan* p) {
     a->WM = frags;
     a->WN = a->NRB = 1;
     p->threads = 64 * frags;
-    p->grid_x = (int)((a->F + 15) / 16);
+    res_grid((a->F + 15) / 16, p);
     p->lds = (size_t)2 * p->run * 17 * es;
     return;
   }
@@ -560,7 +568,7 @@ void res_plan(int prec, int form, bool ph, int cls, ResArgs* a, ResPlan* p) {
   if (lds() > MAX_LDS) p->nf = 1;
   const int nt = 16 * p->nf * a->WN;
   p->threads = 64 * a->WM * a->WN;
-  p->grid_x = (int)((a->F + nt - 1) / nt);
+  res_grid((a->F + nt - 1) / nt, p);
   p->lds = lds();
 }
 

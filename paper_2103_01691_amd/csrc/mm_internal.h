@@ -174,7 +174,8 @@ constexpr size_t MAX_LDS = 160 * 1024;
 // LDS rows of a tile: whole operator units and one K-block that is read ahead.
 inline int res_lds_rows(int n) { return (n + 15) / 16 * 16 + 4; }
 struct ResPlan {
-  int prec, form, mf, nf, ph, threads, grid_x;
+  int prec, form, mf, nf, ph, threads;
+  int grid_x, grid_y;    // tile y * grid_x + x; those past the last fibre have nothing to do
   int run;               // 32 or 64 rows: the operator stays in registers over the products (0: no)
   size_t lds;
 };

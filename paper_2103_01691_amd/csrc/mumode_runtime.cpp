@@ -408,7 +408,7 @@ mm_status run_mode(mm_ctx ctx, const void* in, void* out, const int64_t* dims, i
     mm::res_plan(plan.prec, res_form(L, dt), plan.pro || plan.epi, force, &r, &plan.rp);
     plan.cls = force >= 0 ? std::min(force, 3) : plan.rp.mf - 1;
     plan.grid_x = plan.rp.grid_x;
-    plan.grid_y = 1;
+    plan.grid_y = plan.rp.grid_y;
     plan.threads = plan.rp.threads;
     if (plan_out) *plan_out = plan;
     if (dry) return MM_OK;

@@ -198,7 +198,7 @@ void batch_failed_rebuild() {
 // that they take, for few to very many fibres and every forced tile class.
 template <typename Check>
 void for_all_plans(Check&& check) {
-  const int64_t fibres[] = {1, 100, 8191, 16384, 40000, 65537, (int64_t)1 << 30};
+  const int64_t fibres[] = {1, 100, 8191, 16384, 40000, 65537, 359000000, ((int64_t)1 << 30) + 1};
   for (int prec : {(int)mm::KP_F64, (int)mm::KP_F32})
     for (int form : {(int)mm::RF_C3, (int)mm::RF_RC, (int)mm::RF_RR, (int)mm::RF_C4}) {
       if (form == mm::RF_C4 && prec == mm::KP_F64) continue;
@@ -236,7 +236,8 @@ void resident_plans_fit() {
     if (p.run) EXPECT(p.lds == 2 * p.run * 17 * es && a.n <= p.run && a.WM * 16 >= a.m, WHAT);
     else EXPECT(p.lds >= (size_t)(a.n + 4) * (nt + 1) * es && a.WM * p.mf * 16 * a.NRB >= a.m, WHAT);
     EXPECT(p.mf >= 1 && p.mf <= 4 && (p.nf == 1 || (p.nf == 2 && p.form == mm::RF_RR)), WHAT);
-    EXPECT((int64_t)p.grid_x * nt >= a.F && (int64_t)(p.grid_x - 1) * nt < a.F, WHAT);
+    EXPECT((int64_t)p.grid_x * p.grid_y * nt >= a.F && (int64_t)(p.grid_x - 1) * p.grid_y * nt < a.F, WHAT);
+    EXPECT((int64_t)p.grid_x * p.threads < (int64_t)1 << 32 && p.grid_y < 65536, WHAT);
   });
 }
 
@@ -264,6 +265,24 @@ void flat_operators() {
   mm_destroy(c);
 }
 
+// States of 10^9 fibres and more: more threads than one grid dimension takes.
+void very_many_fibres() {
+  struct { std::vector<int64_t> dims; int mu; mm_dtype dt; mm_prec prec; bool cplx; } cases[] = {
+      {{33, 19000, 19000}, 1, MM_C64, MM_PREC_FP32, true},   {{33, 19000, 19000}, 1, MM_C128, MM_PREC_FP64, true},
+      {{32768, 1, 32769}, 2, MM_C64, MM_PREC_FP32, false},   {{2, 65536, 65536}, 1, MM_R32, MM_PREC_FP32, false},
+      {{40, 16384, 32768}, 1, MM_R32, MM_PREC_FP32, false}};
+  mm_ctx c = open_ctx();
+  for (const auto& t : cases) {
+    mm_tensor T = tensor(t.dims, t.dt);
+    mm_op E[MM_MAXD] = {};
+    E[t.mu - 1] = make_op(c, t.dims[t.mu - 1], t.dims[t.mu - 1], t.cplx, t.prec);
+    for (int nsteps = 1; nsteps <= 2; ++nsteps)
+      EXPECT(mumode_expstep(c, &T, E, nsteps, nullptr) == MM_OK, "%lld entries: %s", (long long)t.dims[t.mu - 1],
+             mm_last_error(c));
+  }
+  mm_destroy(c);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -271,6 +290,7 @@ int main(int argc, char** argv) {
       {"batch_failed_rebuild", batch_failed_rebuild},
       {"resident_plans_fit", resident_plans_fit},
       {"flat_operators", flat_operators},
+      {"very_many_fibres", very_many_fibres},
   };
   const auto it = scenarios.find(argc > 1 ? argv[1] : "");
   if (it == scenarios.end()) return 2;

@@ -26,7 +26,8 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("scenario", ["batch_failed_rebuild", "resident_plans_fit", "flat_operators"])
+@pytest.mark.parametrize("scenario", ["batch_failed_rebuild", "resident_plans_fit", "flat_operators",
+                                      "very_many_fibres"])
 def test_host_runtime(program, scenario):
     r = subprocess.run([program, scenario], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout + r.stderr
