@@ -24,6 +24,7 @@ struct {
   size_t budget = (size_t)1 << 40, used = 0;
   long fail_at = -1;                 // index of the hipMalloc that fails from here on (-1: none)
   long mallocs = 0, frees = 0, launches = 0;
+  struct { dim3 grid, block; size_t lds; hipStream_t stream; } config;
   hipError_t last = hipSuccess;      // what hipGetLastError reports once
   std::map<void*, size_t> live;
   std::map<const void*, int> max_lds;
@@ -110,6 +111,18 @@ hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 1.0f; 
 hipError_t hipFuncSetAttribute(const void* fn, hipFuncAttribute, int bytes) {
   if (bytes > 160 * 1024) return hipErrorInvalidValue;
   rt.max_lds[fn] = bytes;
+  return hipSuccess;
+}
+// the launch configuration between a launch statement and its stub
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, hipStream_t s) {
+  rt.config = {grid, block, lds, s};
+  return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipStream_t* s) {
+  *grid = rt.config.grid;
+  *block = rt.config.block;
+  *lds = rt.config.lds;
+  *s = rt.config.stream;
   return hipSuccess;
 }
 hipError_t hipLaunchKernel(const void* fn, dim3 grid, dim3 block, void**, size_t lds, hipStream_t) {
