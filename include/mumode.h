@@ -223,7 +223,8 @@ mm_status gpe_strang_step_noalloc(mm_ctx ctx, mm_tensor* psi, const mm_op* E, do
  * Lh[k] is formed on the device in FP64 from the operators' masters when the
  * operators, tau or the precision differ from the previous call on this
  * context (for MM_PREC_SPLIT_FP16X2 that formation reads the largest entry
- * back and synchronises `stream` once); later calls with the same ones reuse
+ * back and synchronises `stream` once, for MM_PREC_FP32 the distance from the
+ * identity, unless the stream is being captured); later calls with the same ones reuse
  * it.  The node squares are uploaded only when the nodes change.  P is
  * separable over the modes, so each step folds it into the operators as
  * diagonal factors (re-prepared on the device every step when eps != 0) and

@@ -196,8 +196,10 @@ __global__ void prepare_kernel(const double* __restrict__ master, int64_t rows, 
 template <int LY>
 __global__ void prepare_jobs_kernel(ExpmBatch b, const double* __restrict__ exps, int KBT, int MFT) {
   const ExpmJob& j = b.j[blockIdx.y];
+  PhaseScale ph;
+  ph.minus_id = j.minus_id;
   prepare_any<LY>((int64_t)blockIdx.x * blockDim.x + threadIdx.x, exps + (int64_t)blockIdx.y * b.n * b.n * 2, b.n, b.n,
-                  b.n, 1, PhaseScale(), j.out, KBT, MFT, j.a_exp);
+                  b.n, 1, ph, j.out, KBT, MFT, j.a_exp);
 }
 
 // Per-step operators of the time-dependent harmonic-oscillator splitting
@@ -212,6 +214,7 @@ __global__ void prepare_steps_kernel(StepPrep p) {
   PhaseScale ph;
   ph.rx2 = m.x2;
   ph.cx2 = m.x2;
+  ph.minus_id = m.minus_id;
   ph.cc = 0.5 * p.eps * (cos(t) - cos(th));           // first half step: columns
   ph.rc = 0.5 * p.eps * (cos(th) - cos(t + p.tau));   // second half step: rows
   prepare_any<PR>((int64_t)blockIdx.x * blockDim.x + threadIdx.x, m.master, m.n, m.n, m.n, 1, ph,
@@ -334,6 +337,28 @@ __global__ __launch_bounds__(NORM_THREADS) void maxabs_final_kernel(const uint32
   }
   // slot 0 gets the bound (word 0; its other words and slots 1, 2 cleared)
   for (int i = threadIdx.x; i < 3 * SMAX_WORDS; i += NORM_THREADS) slots[i * SMAX_STRIDE] = i == 0 ? red[0] : 0u;
+}
+
+// ||L - I||_F^2 and ||L||_F^2 (one workgroup)
+__global__ __launch_bounds__(NORM_THREADS) void identity_norms_kernel(const double* __restrict__ L, int n,
+                                                                      double* __restrict__ out) {
+  __shared__ double red[2][NORM_THREADS];
+  double off = 0.0, all = 0.0;
+  for (int e = threadIdx.x; e < n * n; e += NORM_THREADS) {
+    const double re = L[2 * e], im = L[2 * e + 1];
+    const double dr = e % n == e / n ? re - 1.0 : re;
+    off += dr * dr + im * im;
+    all += re * re + im * im;
+  }
+  red[0][threadIdx.x] = off;
+  red[1][threadIdx.x] = all;
+  __syncthreads();
+  for (int w = NORM_THREADS / 2; w > 0; w >>= 1) {
+    if (threadIdx.x < w)
+      for (int k = 0; k < 2; ++k) red[k][threadIdx.x] += red[k][threadIdx.x + w];
+    __syncthreads();
+  }
+  if (threadIdx.x < 2) out[threadIdx.x] = red[threadIdx.x][0];
 }
 
 // ------------------------------------------------------ device expm ------
@@ -869,6 +894,11 @@ hipError_t launch_hermite_collapse(const double* Phi, const double* Psi, int m, 
   const int64_t n = (int64_t)m * m;
   hipLaunchKernelGGL(hermite_collapse_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, Phi, Psi, m, K, tau,
                      out);
+  return hipGetLastError();
+}
+
+hipError_t launch_identity_norms(const double* L, int n, double* out, hipStream_t s) {
+  hipLaunchKernelGGL(identity_norms_kernel, dim3(1), dim3(NORM_THREADS), 0, s, L, n, out);
   return hipGetLastError();
 }
 

@@ -264,6 +264,7 @@ struct StepPrepMode {
   char* out = nullptr;              // step s at out + s * stride
   size_t stride = 0;
   int KBT = 0, MFT = 0, a_exp = 0;
+  int minus_id = 0;                 // resident layouts: prepare L - I
 };
 struct StepPrep {
   StepPrepMode m[MAX_STEP_MODES];
@@ -301,6 +302,7 @@ struct ExpmJob {
   double gr, gi, fr, fi;
   void* out;               // prepared operator of launch_prepare_jobs
   int a_exp;
+  int minus_id;            // resident layouts: prepare the exponential - I
 };
 struct ExpmBatch {
   int n, nb, q;
@@ -314,6 +316,9 @@ hipError_t launch_prepare_jobs(int lay, const ExpmBatch& b, const double* exps, 
 // FP64 device masters with ld = rows; out: m x m complex FP64 interleaved).
 hipError_t launch_hermite_collapse(const double* Phi, const double* Psi, int m, int K, double tau, double* out,
                                    hipStream_t s);
+// out[0] = ||L - I||_F^2, out[1] = ||L||_F^2 of a complex FP64 n x n matrix
+// (column-major, interleaved).
+hipError_t launch_identity_norms(const double* L, int n, double* out, hipStream_t s);
 // Exact nonlinear flow of the Section 4.5 vortex problem over time s on a
 // complex state (interleaved, d modes, column-major): v <- exp((i s/2)(1 -
 // W^-1 |v|^2)) v with W^-1 = prod_k winv[k * 4096 + i_k] (device array).

@@ -111,6 +111,7 @@ struct mm_ctx_s {
     int prec = -1;
     double* master = nullptr;
     size_t master_bytes = 0;
+    double off = -1.0, all = 0.0;   // FP32: ||L - I||_F^2, ||L||_F^2 of the collapsed propagator (-1: not known)
     mm_op_s op;
   };
   HoMode ho[MM_MAXD];
@@ -573,6 +574,16 @@ mm_status grow(mm_ctx ctx, void** p, size_t* have, size_t need) {
   return MM_OK;
 }
 
+// Form of a complex resident operator whose caller prepares it per step: L - I
+// where ||L - I||_F < 1.22 ||L||_F is known, else L itself, which FP32 takes in
+// four products (the rule and the errors of mm_op_prepare_ex; FP64 keeps three
+// products on L, whose error there is that of the block form within 8 %).
+void set_form(mm_op_s* o, bool near) {
+  const bool f32 = o->prec == MM_PREC_FP32;
+  o->res_id = f32 && near ? 1 : 0;
+  o->res_c4 = f32 && !near ? 1 : 0;
+}
+
 // A throw-away operator record for products with a device-resident FP64
 // master that is prepared by the caller (prep_override of run_mode).
 mm_op_s scratch_op(int n, mm_prec prec, int a_exp) {
@@ -582,6 +593,7 @@ mm_op_s scratch_op(int n, mm_prec prec, int a_exp) {
   o.prec = prec;
   o.a_exp = a_exp;
   o.lay = op_layout(prec, n, n, 1);
+  set_form(&o, false);
   layout_blocks(o.lay, n, n, 1, &o.KBT, &o.MFT);
   return o;
 }
@@ -627,7 +639,7 @@ mm_status expm_device(mm_ctx ctx, int n, const double* A, const double* d, doubl
     b.n = n;
     b.nb = 1;
     b.q = q;
-    b.j[0] = {A, d, gr, gi, fr, fi, nullptr, 0};
+    b.j[0] = {A, d, gr, gi, fr, fi, nullptr, 0, 0};
     double* r = nullptr;
     HIPCHK(ctx, mm::launch_expm_batch(b, ctx->ex_buf, &r, s));
     HIPCHK(ctx, hipMemcpyAsync(out, r, sizeof(double) * mat, hipMemcpyDeviceToDevice, s));
@@ -954,7 +966,8 @@ mm_status mm_op_prepare_ex(mm_ctx ctx, const mm_matrix* M, mm_prec prec, unsigne
   }
   // Form of a complex operator on the resident-tile kernels.  Square ones with
   // ||L - I||_F < 1.22 ||L||_F run on L - I in three products and add the
-  // input back; others run as they are, FP32 in four products.  Why: the third
+  // input back; others run as they are, FP32 in four products (so do FP32
+  // operators that the caller keeps as L - I further from it).  Why: the third
   // product rounds at the size of |x + y|, where the block form rounds at that
   // of its result.  Relative L2 errors in FP32 against 64 bits (block form /
   // three products on L / on L - I), by the ratio of the norms: GPE n = 100,
@@ -965,7 +978,8 @@ mm_status mm_op_prepare_ex(mm_ctx ctx, const mm_matrix* M, mm_prec prec, unsigne
   // bits as far as that reference reaches, 5e-15 both ways).
   bool res_id = false, res_c4 = false;
   if (cplx && is_res(op_layout(prec, M->rows, M->cols, cplx))) {
-    if (M->rows == M->cols && !idsplit) {
+    bool near = false;
+    if (M->rows == M->cols) {
       double all = 0.0, off = 0.0;
       for (int64_t j = 0; j < M->cols; ++j)
         for (int64_t i = 0; i < M->rows; ++i) {
@@ -974,9 +988,10 @@ mm_status mm_op_prepare_ex(mm_ctx ctx, const mm_matrix* M, mm_prec prec, unsigne
           all += v[0] * v[0] + v[1] * v[1];
           off += dr * dr + v[1] * v[1];
         }
-      res_id = off < 1.5 * all;
+      near = off < 1.5 * all;
     }
-    res_c4 = prec == MM_PREC_FP32 && !res_id && !idsplit;
+    res_id = near && !idsplit;
+    res_c4 = prec == MM_PREC_FP32 && !near;
   }
   const double rmax = *std::max_element(rsum.begin(), rsum.end());
   if (idsplit)   // L - I in FP64: the products carry only the departure from identity
@@ -1307,10 +1322,33 @@ mm_status ho_strang_step(mm_ctx ctx, mm_tensor* psi, const mm_op* Phi_fwd, const
       for (double v : h) amax = std::max(amax, std::fabs(v));
       H.op.a_exp = mm::fp16x2_op_exp(amax);
     }
+    H.off = -1.0;
+    if (H.op.lay == mm::KY_RES32) {
+      // distance from the identity, for the form of its products (one read-back
+      // per formation; a formation under capture goes without)
+      hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+      HIPCHK(ctx, hipStreamIsCapturing(s, &cap));
+      if (cap == hipStreamCaptureStatusNone) {
+        HIPCHK(ctx, mm::launch_identity_norms(H.master, n, ctx->red_result, s));
+        HIPCHK(ctx, hipMemcpyAsync(ctx->host_result, ctx->red_result, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
+        HIPCHK(ctx, hipStreamSynchronize(s));
+        H.off = ctx->host_result[0];
+        H.all = ctx->host_result[1];
+      }
+    }
     H.phi = F;
     H.psi = B;
     H.tau = tau;
     H.prec = (int)F->prec;
+  }
+  // with the potential's phases, at most theta = eps min(tau / 4, 1) max x^2 on
+  // rows and on columns: ||P L P - I|| <= ||L - I|| + 2 theta ||L||
+  for (int k = 0; k < psi->d; ++k) {
+    const mm_ctx_s::HoMode& H = ctx->ho[k];
+    double x2 = 0.0;
+    for (int64_t i = 0; i < psi->dims[k]; ++i) x2 = std::max(x2, nodes[k][i] * nodes[k][i]);
+    const double theta = std::fabs(eps) * std::min(0.25 * std::fabs(tau), 1.0) * x2;
+    set_form(&ctx->ho[k].op, H.off >= 0.0 && std::sqrt(H.off) + 2.0 * theta * std::sqrt(H.all) < std::sqrt(1.5 * H.all));
   }
   // squared node coordinates, uploaded when the nodes change (from pinned
   // staging, once the previous upload from it has completed)
@@ -1392,6 +1430,7 @@ mm_status ho_strang_step(mm_ctx ctx, mm_tensor* psi, const mm_op* Phi_fwd, const
         m.KBT = L.KBT;
         m.MFT = L.MFT;
         m.a_exp = L.a_exp;
+        m.minus_id = L.res_id;
         done[k] = true;
       }
       HIPCHK(ctx, mm::launch_prepare_steps(ctx->ho[k0].op.lay, p, s));
@@ -2140,6 +2179,10 @@ mm_status mumode_magnus_step(mm_ctx ctx, mm_tensor* T, const mm_matrix* B, const
     // radii sum_{j != i} |b_ij + conj(b_ji)| / 2
     std::vector<double> hc, hr;
     std::vector<int> aexp;   // FP16X2 scale of each prepared exponential
+    // FP32: squared Frobenius norms of B and of its Hermitian part without the
+    // diagonal; whether each prepared exponential is one less the identity
+    double foff = 0.0, hoff = 0.0;
+    std::vector<char> near;
     mm_op_s op;
   };
   std::vector<Mode> modes(d);
@@ -2206,6 +2249,14 @@ mm_status mumode_magnus_step(mm_ctx ctx, mm_tensor* T, const mm_matrix* B, const
       M.bnorm = std::max(M.bnorm, sum);
     }
     if (check != 0.0) return fail(ctx, MM_ERR_NONFINITE, "B[%d] holds NaN / Inf", k);
+    if (is_res(M.op.lay) && prec == MM_PREC_FP32)
+      for (int j = 0; j < n; ++j)
+        for (int i = 0; i < j; ++i) {
+          const double *a = host + 2 * ((size_t)j * n + i), *b = host + 2 * ((size_t)i * n + j);
+          const double re = a[0] + b[0], im = a[1] - b[1];
+          M.foff += a[0] * a[0] + a[1] * a[1] + b[0] * b[0] + b[1] * b[1];
+          M.hoff += 0.5 * (re * re + im * im);
+        }
     if (prec == MM_PREC_SPLIT_FP16X2) {
       M.hc.assign(n, 0.0);
       M.hr.assign(n, 0.0);
@@ -2289,8 +2340,26 @@ mm_status mumode_magnus_step(mm_ctx ctx, mm_tensor* T, const mm_matrix* B, const
           }
           a_exp = mm::fp16x2_op_exp(std::exp(std::min(700.0, std::fabs(tau) * mu)));
         }
+        // FP32 form: with A = tau (B + g diag(d)) and H its Hermitian part,
+        // ||e^A - I||_F <= ||A||_F e^||H|| and ||e^A||_F >= sqrt(n) e^-||H||
+        bool near = false;
+        if (is_res(M.op.lay) && prec == MM_PREC_FP32) {
+          const double* host = (const double*)((const char*)ctx->mg_stage + M.Boff);
+          double f = M.foff, h = M.hoff;
+          for (int i = 0; i < M.n; ++i) {
+            const double* b = host + 2 * ((size_t)i * M.n + i);
+            const double di = M.timed ? dg[k][i] : 0.0;
+            const double re = b[0] + gr * di, im = b[1] + gi * di;
+            f += re * re + im * im;
+            h += re * re;
+          }
+          near = std::fabs(tau) * std::sqrt(f) * std::exp(2.0 * std::fabs(tau) * std::sqrt(h)) <
+                 std::sqrt(1.5 * M.n);
+        }
         if ((int)M.aexp.size() <= j) M.aexp.resize(j + 1);
+        if ((int)M.near.size() <= j) M.near.resize(j + 1);
         M.aexp[j] = a_exp;
+        M.near[j] = near;
         const double* A = (const double*)((char*)ctx->mg_buf + M.Boff);
         const double* dd = M.timed ? (const double*)((char*)ctx->mg_buf + M.doff) : nullptr;
         void* out = (char*)ctx->mg_prep + M.poff + (size_t)j * M.pb;
@@ -2311,7 +2380,7 @@ mm_status mumode_magnus_step(mm_ctx ctx, mm_tensor* T, const mm_matrix* B, const
         batch.n = M.n;
         batch.q = q;
         bop = &M.op;
-        batch.j[batch.nb++] = {A, dd, gr, gi, tau, 0.0, out, a_exp};
+        batch.j[batch.nb++] = {A, dd, gr, gi, tau, 0.0, out, a_exp, near};
       }
     }
     if ((st = flush()) != MM_OK) return st;
@@ -2323,6 +2392,7 @@ mm_status mumode_magnus_step(mm_ctx ctx, mm_tensor* T, const mm_matrix* B, const
         const int j = M.timed ? it - it0 : 0;
         const void* P = (char*)ctx->mg_prep + M.poff + (size_t)j * M.pb;
         M.op.a_exp = M.aexp[j];
+        set_form(&M.op, M.near[j]);
         mm::ModePlan plan;
         st = run_mode(ctx, cur, cur, T->dims, d, T->dtype, &M.op, k + 1, 0, 0, s, &plan, true, P);
         if (st != MM_OK) return st;
