@@ -1308,6 +1308,8 @@ mm_status ho_strang_step(mm_ctx ctx, mm_tensor* psi, const mm_op* Phi_fwd, const
     const mm_op F = Phi_fwd[k], B = Psi_bwd[k];
     if (H.phi == F && H.psi == B && H.tau == tau && H.prec == (int)F->prec) continue;
     const int n = (int)psi->dims[k];
+    // (a formation that fails leaves none: the master may be gone)
+    H.phi = H.psi = nullptr;
     st = grow(ctx, (void**)&H.master, &H.master_bytes, sizeof(double) * 2 * (size_t)n * n);
     if (st != MM_OK) return st;
     HIPCHK(ctx, mm::launch_hermite_collapse(F->dev_master, B->dev_master, n, (int)F->rows, tau, H.master, s));

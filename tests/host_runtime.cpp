@@ -300,6 +300,44 @@ void very_many_fibres() {
   mm_destroy(c);
 }
 
+struct Oscillator {
+  mm_op F[MM_MAXD], B[MM_MAXD];
+  std::vector<double> x;
+  const double* nodes[MM_MAXD];
+  mm_tensor T;
+};
+Oscillator oscillator(mm_ctx c, int64_t n, mm_prec prec) {
+  Oscillator o = {};
+  for (int k = 0; k < 3; ++k) {
+    o.F[k] = make_op(c, n, n, false, prec);
+    o.B[k] = make_op(c, n, n, false, prec);
+  }
+  o.x.resize(n);
+  for (int64_t i = 0; i < n; ++i) o.x[i] = 0.1 * (double)i;
+  o.T = tensor({n, n, n}, prec == MM_PREC_FP64 ? MM_C128 : MM_C64);
+  return o;
+}
+mm_status step(mm_ctx c, Oscillator& o, int nsteps) {
+  for (int k = 0; k < 3; ++k) o.nodes[k] = o.x.data();
+  return ho_strang_step(c, &o.T, o.F, o.B, o.nodes, 0.1, 0.02, 0.1, nsteps, nullptr);
+}
+
+// A formation that runs out of memory is not taken for the one before.
+void oscillator_failed_formation() {
+  mm_ctx c = open_ctx();
+  Oscillator a = oscillator(c, 32, MM_PREC_FP64), b = oscillator(c, 96, MM_PREC_FP64);
+  long n = rt.launches;
+  EXPECT(step(c, a, 1) == MM_OK, "%s", mm_last_error(c));
+  const long first = rt.launches - n;
+  rt.fail_at = rt.mallocs;
+  EXPECT(step(c, b, 1) == MM_ERR_NOMEM, "no failure");
+  rt.fail_at = -1;
+  n = rt.launches;
+  EXPECT(step(c, a, 1) == MM_OK, "%s", mm_last_error(c));
+  EXPECT(rt.launches - n >= first - 2, "%ld launches, %ld with all three modes formed", rt.launches - n, first);
+  mm_destroy(c);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -308,6 +346,7 @@ int main(int argc, char** argv) {
       {"resident_plans_fit", resident_plans_fit},
       {"flat_operators", flat_operators},
       {"very_many_fibres", very_many_fibres},
+      {"oscillator_failed_formation", oscillator_failed_formation},
   };
   const auto it = scenarios.find(argc > 1 ? argv[1] : "");
   if (it == scenarios.end()) return 2;
