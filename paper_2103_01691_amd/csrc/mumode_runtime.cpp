@@ -99,9 +99,10 @@ struct mm_ctx_s {
   void* mg_prep = nullptr;
   double* mg_exp = nullptr;
   size_t mg_bytes = 0, mg_stage_bytes = 0, mg_prep_bytes = 0, mg_exp_bytes = 0;
-  // per-mode scratch for operators re-prepared every step (ho_strang_step)
-  void* step_prep[MM_MAXD] = {nullptr};
-  size_t step_prep_bytes[MM_MAXD] = {0};
+  size_t ex_failed = SIZE_MAX, mg_prep_failed = SIZE_MAX;   // see grow_units
+  // operators re-prepared every step (ho_strang_step), a block of steps of all modes
+  void* step_prep = nullptr;
+  size_t step_prep_bytes = 0, step_prep_failed = SIZE_MAX;   // see grow_units
   // ho_strang_step: per mode, the collapsed propagator Psi diag(exp(-i tau
   // (k + 1/2))) Phi (FP64 complex master on the device) for the operators,
   // tau and precision of the last call that formed it
@@ -574,6 +575,22 @@ mm_status grow(mm_ctx ctx, void** p, size_t* have, size_t need) {
   return MM_OK;
 }
 
+// Grow a buffer to `fixed` bytes and *units blocks of `unit` bytes, or to as
+// many blocks as there is memory for, `least` at the least (*units is lowered).
+// *failed keeps the smallest size that could not be had, which later calls do
+// not try again: a buffer that is large enough for the fewer blocks stays.
+mm_status grow_units(mm_ctx ctx, void** p, size_t* have, size_t* failed, size_t fixed, size_t unit, int* units,
+                     int least) {
+  auto bytes = [&]() { return fixed + unit * (size_t)*units; };
+  while (*units > least && bytes() > *have && bytes() >= *failed) *units = std::max(least, *units / 2);
+  for (;;) {
+    const mm_status st = grow(ctx, p, have, bytes());
+    if (st != MM_ERR_NOMEM || *units <= least) return st;
+    *failed = std::min(*failed, bytes());
+    *units = std::max(least, *units / 2);
+  }
+}
+
 // Form of a complex resident operator whose caller prepares it per step: L - I
 // where ||L - I||_F < 1.22 ||L||_F is known, else L itself, which FP32 takes in
 // four products (the rule and the errors of mm_op_prepare_ex; FP64 keeps three
@@ -887,8 +904,7 @@ mm_status mm_destroy(mm_ctx ctx) {
     hipEventDestroy(r.b);
   }
   if (ctx->ws && !ctx->ws_user) hipFree(ctx->ws);
-  for (int k = 0; k < MM_MAXD; ++k)
-    if (ctx->step_prep[k]) hipFree(ctx->step_prep[k]);
+  if (ctx->step_prep) hipFree(ctx->step_prep);
   if (ctx->x2) hipFree(ctx->x2);
   if (ctx->x2_stage) hipHostFree(ctx->x2_stage);
   if (ctx->x2_ev) hipEventDestroy(ctx->x2_ev);
@@ -1390,26 +1406,14 @@ mm_status ho_strang_step(mm_ctx ctx, mm_tensor* psi, const mm_op* Phi_fwd, const
   while (blk > 1 && per_step * blk > ((size_t)64 << 20)) blk /= 2;
   // (the buffers hold a whole block from the first call on: growing them for
   // a call of more steps costs 1 ms of waiting, freeing and allocating, as
-  // much as 17 steps at n = 128)
-  for (int k = 0; k < psi->d; ++k) {
-    size_t want = need[k] * blk;
-    if (ctx->step_prep_bytes[k] < want) {
-      if (ctx->step_prep[k]) {
-        HIPCHK(ctx, hipDeviceSynchronize());
-        HIPCHK(ctx, hipFree(ctx->step_prep[k]));
-        ctx->step_prep[k] = nullptr;
-        ctx->step_prep_bytes[k] = 0;
-      }
-      if (hipMalloc(&ctx->step_prep[k], want) != hipSuccess) {
-        // no room for a whole block: this call's steps
-        (void)hipGetLastError();
-        blk = std::min(blk, std::max(nsteps, 1));
-        want = need[k] * blk;
-        if (hipMalloc(&ctx->step_prep[k], want) != hipSuccess) return fail(ctx, MM_ERR_NOMEM, "step operators");
-      }
-      ctx->step_prep_bytes[k] = want;
-    }
-  }
+  // much as 17 steps at n = 128; where there is no room for one, they hold
+  // this call's steps)
+  st = grow_units(ctx, &ctx->step_prep, &ctx->step_prep_bytes, &ctx->step_prep_failed, 0, per_step, &blk,
+                  std::min(blk, std::max(nsteps, 1)));
+  if (st != MM_OK) return st;
+  char* prep_of[MM_MAXD];   // step j of mode k: prep_of[k] + j * need[k]
+  for (int k = 0; k < psi->d; ++k)
+    prep_of[k] = k == 0 ? (char*)ctx->step_prep : prep_of[k - 1] + need[k - 1] * blk;
   auto prepare_block = [&](int it0, int steps) -> mm_status {
     // one launch per operator layout
     bool done[MM_MAXD] = {false};
@@ -1427,7 +1431,7 @@ mm_status ho_strang_step(mm_ctx ctx, mm_tensor* psi, const mm_op* Phi_fwd, const
         m.master = L.dev_master;
         m.n = L.rows;
         m.x2 = ctx->x2 + (size_t)k * 4096;
-        m.out = (char*)ctx->step_prep[k];
+        m.out = prep_of[k];
         m.stride = need[k];
         m.KBT = L.KBT;
         m.MFT = L.MFT;
@@ -1451,7 +1455,7 @@ mm_status ho_strang_step(mm_ctx ctx, mm_tensor* psi, const mm_op* Phi_fwd, const
     void* cur = psi->data;
     for (int k = 0; k < psi->d; ++k) {
       mm_op_s* L = &ctx->ho[k].op;
-      const void* prep = (const char*)ctx->step_prep[k] + sidx * need[k];
+      const void* prep = prep_of[k] + sidx * need[k];
       mm::ModePlan plan;
       st = run_mode(ctx, cur, cur, psi->dims, psi->d, psi->dtype, L, k + 1, 0, 0, s, &plan, true);
       if (st != MM_OK) return st;

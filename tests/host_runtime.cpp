@@ -322,6 +322,28 @@ mm_status step(mm_ctx c, Oscillator& o, int nsteps) {
   return ho_strang_step(c, &o.T, o.F, o.B, o.nodes, 0.1, 0.02, 0.1, nsteps, nullptr);
 }
 
+// The oscillator step where a whole block of step operators does not fit: the
+// call's own steps do, for all modes together, and a buffer that holds them
+// stays from call to call.
+void oscillator_little_memory() {
+  mm_ctx c = open_ctx();
+  Oscillator o = oscillator(c, 128, MM_PREC_FP64);
+  const size_t before = rt.used;
+  EXPECT(step(c, o, 2) == MM_OK, "%s", mm_last_error(c));
+  const size_t whole = rt.used - before;   // formation, nodes, a block of steps
+  mm_destroy(c);
+  c = open_ctx();
+  o = oscillator(c, 128, MM_PREC_FP64);
+  rt.budget = rt.used + whole / 3;
+  EXPECT(step(c, o, 2) == MM_OK, "%s", mm_last_error(c));
+  const long mallocs = rt.mallocs, frees = rt.frees;
+  for (int i = 0; i < 3; ++i) EXPECT(step(c, o, 2) == MM_OK, "%s", mm_last_error(c));
+  EXPECT(rt.mallocs == mallocs && rt.frees == frees, "%ld allocations, %ld frees in repeated calls",
+         rt.mallocs - mallocs, rt.frees - frees);
+  EXPECT(step(c, o, 3) == MM_OK, "%s", mm_last_error(c));
+  mm_destroy(c);
+}
+
 // A formation that runs out of memory is not taken for the one before.
 void oscillator_failed_formation() {
   mm_ctx c = open_ctx();
@@ -346,6 +368,7 @@ int main(int argc, char** argv) {
       {"resident_plans_fit", resident_plans_fit},
       {"flat_operators", flat_operators},
       {"very_many_fibres", very_many_fibres},
+      {"oscillator_little_memory", oscillator_little_memory},
       {"oscillator_failed_formation", oscillator_failed_formation},
   };
   const auto it = scenarios.find(argc > 1 ? argv[1] : "");
