@@ -615,15 +615,6 @@ mm_op_s scratch_op(int n, mm_prec prec, int a_exp) {
   return o;
 }
 
-// out = exp(f (A + g diag(d))) for a complex n x n FP64 matrix A on the
-// device (d real, nullable), by scaling and squaring of the Taylor
-// polynomial: X = f (A + g diag d) / 2^q with ||X||_1 <= 1, the degree-18
-// Taylor polynomial (truncation <= e/19! < 2.2e-17) evaluated by the
-// Paterson-Stockmeyer scheme with blocks of four terms (X^2, X^3, X^4, then
-// Horner in X^4: 7 matrix products instead of 18), then q squarings.  Every
-// matrix product is a mode-1 product of the FP64 MFMA kernel.  bound: an
-// upper bound of ||A + g diag d||_1 known to the caller, or < 0 to compute
-// it here (synchronises s).
 // Squarings that scale fa = |f| ||A + g diag d||_1 to at most 1.
 mm_status expm_squarings(mm_ctx ctx, double fa, int* q) {
   *q = 0;
@@ -633,12 +624,34 @@ mm_status expm_squarings(mm_ctx ctx, double fa, int* q) {
   return MM_OK;
 }
 
+// Buffers of one exponential of an n x n matrix; keep: also the result's.
+mm_status expm_buffers(mm_ctx ctx, int n, bool keep) {
+  const size_t mat = sizeof(double) * 2 * (size_t)n * n;
+  mm_status st = grow(ctx, (void**)&ctx->ex_buf, &ctx->ex_bytes,
+                      std::max(mm::expm_batch_bytes(n, 1), 6 * mat) + sizeof(double) * n);
+  if (st == MM_OK && n > mm::EXPM_MAX_N) {
+    const mm_op_s op = scratch_op(n, MM_PREC_FP64, 0);
+    st = grow(ctx, &ctx->ex_prep, &ctx->ex_prep_bytes, 2 * mm::prepared_bytes(op.lay, op.KBT, op.MFT));
+  }
+  if (st == MM_OK && keep) st = grow(ctx, (void**)&ctx->mg_exp, &ctx->mg_exp_bytes, mat);
+  return st;
+}
+
+// out = exp(f (A + g diag(d))) for a complex n x n FP64 matrix A on the
+// device (d real, nullable), by scaling and squaring of the Taylor
+// polynomial: X = f (A + g diag d) / 2^q with ||X||_1 <= 1, the degree-18
+// Taylor polynomial (truncation <= e/19! < 2.2e-17) evaluated by the
+// Paterson-Stockmeyer scheme with blocks of four terms (X^2, X^3, X^4, then
+// Horner in X^4: 7 matrix products instead of 18), then q squarings.  Up to
+// EXPM_MAX_N rows it is a batch of one (kern_expm.hip), above every matrix
+// product is a mode-1 product of the FP64 MFMA kernel.  bound: an upper bound
+// of ||A + g diag d||_1 known to the caller, or < 0 to compute it here
+// (synchronises s).
 mm_status expm_device(mm_ctx ctx, int n, const double* A, const double* d, double gr, double gi, double fr,
                       double fi, double bound, double* out, hipStream_t s) {
   const size_t mat = (size_t)n * n * 2;
   const bool small = n <= mm::EXPM_MAX_N;
-  mm_status st = grow(ctx, (void**)&ctx->ex_buf, &ctx->ex_bytes,
-                      std::max(mm::expm_batch_bytes(n, 1), sizeof(double) * 6 * mat) + sizeof(double) * n);
+  mm_status st = expm_buffers(ctx, n, false);
   if (st != MM_OK) return st;
   double* cs = ctx->ex_buf + 6 * mat;
   if (bound < 0) {
@@ -664,8 +677,6 @@ mm_status expm_device(mm_ctx ctx, int n, const double* A, const double* d, doubl
   }
   mm_op_s op = scratch_op(n, MM_PREC_FP64, 0);
   const size_t pb = mm::prepared_bytes(op.lay, op.KBT, op.MFT);
-  st = grow(ctx, &ctx->ex_prep, &ctx->ex_prep_bytes, 2 * pb);
-  if (st != MM_OK) return st;
   double* X = ctx->ex_buf;
   double* X2 = X + mat;
   double* X3 = X2 + mat;
@@ -2294,13 +2305,18 @@ mm_status mumode_magnus_step(mm_ctx ctx, mm_tensor* T, const mm_matrix* B, const
   int blk = per_step ? std::min(nsteps, 32) : nsteps;
   while (per_step && blk > 1 && per_step * blk > ((size_t)256 << 20)) blk /= 2;
   {
+    // one exponential's buffers first: a block takes what is left
+    for (const Mode& M : modes)
+      if (M.on && (st = expm_buffers(ctx, M.n, M.n > mm::EXPM_MAX_N)) != MM_OK) return st;
+    st = grow_units(ctx, &ctx->mg_prep, &ctx->mg_prep_bytes, &ctx->mg_prep_failed, fixed, per_step, &blk,
+                    per_step ? 1 : blk);
+    if (st != MM_OK) return st;
     size_t at = 0;
     for (Mode& M : modes)
       if (M.on) {
         M.poff = at;
         at += M.pb * (M.timed ? (size_t)blk : 1);
       }
-    if ((st = grow(ctx, &ctx->mg_prep, &ctx->mg_prep_bytes, at)) != MM_OK) return st;
   }
   const size_t bytes = (size_t)numel(T) * dsize(T->dtype);
   for (int it0 = 0; it0 < nsteps; it0 += blk) {
@@ -2310,11 +2326,18 @@ mm_status mumode_magnus_step(mm_ctx ctx, mm_tensor* T, const mm_matrix* B, const
     const mm_op_s* bop = nullptr;
     auto flush = [&]() -> mm_status {
       if (batch.nb == 0) return MM_OK;
-      mm_status r = grow(ctx, (void**)&ctx->ex_buf, &ctx->ex_bytes, mm::expm_batch_bytes(batch.n, batch.nb));
+      int units = batch.nb;   // as many at a time as there is memory for
+      mm_status r = grow_units(ctx, (void**)&ctx->ex_buf, &ctx->ex_bytes, &ctx->ex_failed,
+                               sizeof(double) * batch.n, mm::expm_batch_bytes(batch.n, 1), &units, 1);
       if (r != MM_OK) return r;
-      double* e = nullptr;
-      HIPCHK(ctx, mm::launch_expm_batch(batch, ctx->ex_buf, &e, s));
-      HIPCHK(ctx, mm::launch_prepare_jobs(bop->lay, batch, e, bop->KBT, bop->MFT, s));
+      for (int j0 = 0; j0 < batch.nb; j0 += units) {
+        mm::ExpmBatch part = batch;
+        part.nb = std::min(units, batch.nb - j0);
+        std::copy(batch.j + j0, batch.j + j0 + part.nb, part.j);
+        double* e = nullptr;
+        HIPCHK(ctx, mm::launch_expm_batch(part, ctx->ex_buf, &e, s));
+        HIPCHK(ctx, mm::launch_prepare_jobs(bop->lay, part, e, bop->KBT, bop->MFT, s));
+      }
       batch.nb = 0;
       return MM_OK;
     };
@@ -2370,8 +2393,6 @@ mm_status mumode_magnus_step(mm_ctx ctx, mm_tensor* T, const mm_matrix* B, const
         const double* dd = M.timed ? (const double*)((char*)ctx->mg_buf + M.doff) : nullptr;
         void* out = (char*)ctx->mg_prep + M.poff + (size_t)j * M.pb;
         if (M.n > mm::EXPM_MAX_N) {
-          const size_t eb = sizeof(double) * 2 * (size_t)M.n * M.n;
-          if ((st = grow(ctx, (void**)&ctx->mg_exp, &ctx->mg_exp_bytes, eb)) != MM_OK) return st;
           st = expm_device(ctx, M.n, A, dd, gr, gi, tau, 0.0, bound, ctx->mg_exp, s);
           if (st != MM_OK) return st;
           HIPCHK(ctx, mm::launch_prepare(M.op.lay, 1, ctx->mg_exp, M.n, M.n, M.n, mm::PhaseScale(), out, M.op.KBT,

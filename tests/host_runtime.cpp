@@ -360,6 +360,32 @@ void oscillator_failed_formation() {
   mm_destroy(c);
 }
 
+// The midpoint step where one step's operators and exponentials fit but not a
+// block of them.
+void midpoint_little_memory() {
+  const int64_t n = 128;
+  std::vector<double> g(2 * n * n), d(n, 1.0), coef(2 * 32 * 3, 0.5);
+  for (size_t i = 0; i < g.size(); ++i) g[i] = 1e-3 * (double)(i % 7);
+  const mm_matrix m = {n, n, n, MM_C128, g.data(), 0};
+  const mm_matrix B[3] = {m, m, m};
+  const double* dd[3] = {d.data(), d.data(), d.data()};
+  for (mm_prec prec : {MM_PREC_FP64, MM_PREC_FP32, MM_PREC_SPLIT_BF16X3}) {
+    rt.budget = (size_t)1 << 40;
+    mm_ctx c = open_ctx();
+    mm_tensor T = tensor({n, n, n}, prec == MM_PREC_FP64 ? MM_C128 : MM_C64);
+    // per mode: the generator (16 n^2), one prepared operator and one
+    // exponential with its five helpers (96 n^2)
+    rt.budget = rt.used + (size_t)3 * 16 * n * n + (size_t)3 * 32 * n * n + (size_t)96 * n * n + (1 << 20);
+    EXPECT(mumode_magnus_step(c, &T, B, dd, coef.data(), 0.1, 32, prec, nullptr) == MM_OK, "precision %d: %s", (int)prec,
+           mm_last_error(c));
+    const long mallocs = rt.mallocs, frees = rt.frees;
+    EXPECT(mumode_magnus_step(c, &T, B, dd, coef.data(), 0.1, 32, prec, nullptr) == MM_OK, "%s", mm_last_error(c));
+    EXPECT(rt.mallocs == mallocs && rt.frees == frees, "precision %d: %ld allocations, %ld frees in a repeated call",
+           (int)prec, rt.mallocs - mallocs, rt.frees - frees);
+    mm_destroy(c);
+  }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -370,6 +396,7 @@ int main(int argc, char** argv) {
       {"very_many_fibres", very_many_fibres},
       {"oscillator_little_memory", oscillator_little_memory},
       {"oscillator_failed_formation", oscillator_failed_formation},
+      {"midpoint_little_memory", midpoint_little_memory},
   };
   const auto it = scenarios.find(argc > 1 ? argv[1] : "");
   if (it == scenarios.end()) return 2;
