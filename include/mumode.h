@@ -364,8 +364,11 @@ mm_status mm_tune_get(mm_ctx ctx, int index, int64_t* key6, int* cls, double* us
 /* Forget every recorded entry. */
 mm_status mm_tune_clear(mm_ctx ctx);
 /* Write the entries to a text file / add the entries of such a file (an
- * entry already present is replaced).  MM_ERR_ARG if the file cannot be
- * opened or is malformed (nothing is added then). */
+ * entry already present is replaced).  Files of the first format version are
+ * read without their FP64 and FP32 entries of at most 512 real rows and
+ * columns, whose class numbers meant other tile shapes: those products keep
+ * the built-in choice.  MM_ERR_ARG if the file cannot be opened or is
+ * malformed (nothing is added then). */
 mm_status mm_tune_save(mm_ctx ctx, const char* path);
 mm_status mm_tune_load(mm_ctx ctx, const char* path);
 

@@ -2102,7 +2102,7 @@ mm_status mm_tune_save(mm_ctx ctx, const char* path) {
   if (!ctx || !path) return MM_ERR_ARG;
   FILE* f = std::fopen(path, "w");
   if (!f) return fail(ctx, MM_ERR_ARG, "cannot write %s", path);
-  std::fprintf(f, "mumode-tune 1\n");
+  std::fprintf(f, "mumode-tune 2\n");
   for (const auto& e : ctx->tune)
     std::fprintf(f, "%lld %lld %lld %lld %lld %lld %d %.3f\n", (long long)e.first[0], (long long)e.first[1],
                  (long long)e.first[2], (long long)e.first[3], (long long)e.first[4], (long long)e.first[5],
@@ -2117,7 +2117,7 @@ mm_status mm_tune_load(mm_ctx ctx, const char* path) {
   if (!f) return fail(ctx, MM_ERR_ARG, "cannot read %s", path);
   char head[32] = {0};
   int ver = 0;
-  if (std::fscanf(f, "%31s %d", head, &ver) != 2 || std::strcmp(head, "mumode-tune") != 0 || ver != 1) {
+  if (std::fscanf(f, "%31s %d", head, &ver) != 2 || std::strcmp(head, "mumode-tune") != 0 || (ver != 1 && ver != 2)) {
     std::fclose(f);
     return fail(ctx, MM_ERR_ARG, "%s is not a tune file", path);
   }
@@ -2132,6 +2132,12 @@ mm_status mm_tune_load(mm_ctx ctx, const char* path) {
       std::fclose(f);
       return fail(ctx, MM_ERR_ARG, "%s: bad entry", path);
     }
+    // Version 1 was also written when FP64 and FP32 products of the resident-
+    // tile kernels' sizes ran on the chunked tiles, whose class numbers are other
+    // shapes (class 2, the fastest then for 128 real FP64 rows at 16.6 us, would
+    // be three fragments per wave, 19.3 us; the built-in choice takes 14.9)
+    const bool f64 = k[0] == mm::KP_F64, f32 = k[0] == mm::KP_F32;
+    if (ver == 1 && (f64 || f32) && k[3] <= 512 && k[4] <= 512) continue;
     t[{k[0], k[1], k[2], k[3], k[4], k[5]}] = {c, us};
   }
   const bool eof = n == EOF;

@@ -386,6 +386,30 @@ void midpoint_little_memory() {
   }
 }
 
+// Tune files: of the first version, entries of FP64 / FP32 products that now run
+// on the resident tiles are left out; what is written is read back whole.
+void tune_file_versions() {
+  const char* path = "tune_versions.txt";
+  const char* entries = "0 0 1 128 128 16384 2 16.6\n1 1 0 512 512 4096 0 1.0\n0 0 1 600 600 900 1 9.0\n"
+                        "3 1 0 256 256 16384 6 1.0\n";
+  for (int version = 1; version <= 2; ++version) {
+    FILE* f = std::fopen(path, "w");
+    std::fprintf(f, "mumode-tune %d\n%s", version, entries);
+    std::fclose(f);
+    mm_ctx c = open_ctx();
+    EXPECT(mm_tune_load(c, path) == MM_OK, "%s", mm_last_error(c));
+    int n = 0, again = 0;
+    mm_tune_count(c, &n);
+    EXPECT(n == (version == 1 ? 2 : 4), "version %d: %d entries", version, n);
+    EXPECT(mm_tune_save(c, path) == MM_OK && mm_tune_clear(c) == MM_OK && mm_tune_load(c, path) == MM_OK, "%s",
+           mm_last_error(c));
+    mm_tune_count(c, &again);
+    EXPECT(again == n, "%d of %d entries read back", again, n);
+    mm_destroy(c);
+    std::remove(path);
+  }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -397,6 +421,7 @@ int main(int argc, char** argv) {
       {"oscillator_little_memory", oscillator_little_memory},
       {"oscillator_failed_formation", oscillator_failed_formation},
       {"midpoint_little_memory", midpoint_little_memory},
+      {"tune_file_versions", tune_file_versions},
   };
   const auto it = scenarios.find(argc > 1 ? argv[1] : "");
   if (it == scenarios.end()) return 2;
