@@ -37,15 +37,11 @@ BYTES_PER_PRODUCT = 2 * 8 * N ** D                 # one read and one write of t
 SPLIT_PRODUCTS = {"bf16x3": 6, "fp16x2": 3}        # MFMA products per algorithmic product
 
 
-# sources that determine the split product kernel; HBM traffic counters taken
-# on another build of them are not reported
-KERNEL_SOURCES = ["paper_2103_01691_amd/csrc/mode_tile.h", "paper_2103_01691_amd/csrc/mm_internal.h",
-                  "paper_2103_01691_amd/csrc/kern_bf16x3.hip", "paper_2103_01691_amd/csrc/kern_fp16x2.hip",
-                  "paper_2103_01691_amd/csrc/kern_bf16x3_ida.hip", "paper_2103_01691_amd/csrc/kern_fp16x2_ida.hip",
-                  "paper_2103_01691_amd/csrc/kernels_common.hip", "paper_2103_01691_amd/build.py",
-                  "paper_2103_01691_amd/csrc/mode_gauss.h", "paper_2103_01691_amd/csrc/kern_bf16x3_g.hip",
-                  "paper_2103_01691_amd/csrc/kern_fp16x2_g.hip", "paper_2103_01691_amd/csrc/rsplit.h",
-                  "paper_2103_01691_amd/csrc/kern_rsplit.inl"]
+# sources that determine the kernels; profiles taken on another build of them
+# are not reported
+CSRC = "paper_2103_01691_amd/csrc"
+KERNEL_SOURCES = sorted(f"{CSRC}/{f}" for f in os.listdir(os.path.join(ROOT, CSRC))
+                        if f.endswith((".hip", ".inl", ".h"))) + ["paper_2103_01691_amd/build.py"]
 
 
 def kernel_source_hash():
