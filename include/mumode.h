@@ -62,9 +62,14 @@ typedef enum { MM_R32 = 0, MM_R64 = 1, MM_C64 = 2, MM_C128 = 3 } mm_dtype;
  *  MM_PREC_FP32         FP32 MFMA, FP32 state.
  *                       Complex products of both run in three real products
  *                       (square operators as L - I with the input added back)
- *                       where that is as accurate: an entry of a fibre that
- *                       holds Inf / NaN makes both components of the whole
- *                       output fibre non-finite.
+ *                       where that is as accurate in the 2-norm: an entry of
+ *                       a fibre that holds Inf / NaN makes both components of
+ *                       the whole output fibre non-finite, sums of the two
+ *                       components of an entry, and differences of an operator
+ *                       from the identity, must stay in the type's range
+ *                       (entries up to half its largest value do), and a
+ *                       component that is much smaller than its partner is
+ *                       accurate to the size of the entry, not to its own.
  *  MM_PREC_SPLIT_BF16X3 operator and state split into three RNE bfloat16
  *                       pieces each (x = x0 + x1 + x2); the six piece
  *                       products x_a y_b with a + b <= 2 run on BF16 MFMA with
@@ -378,7 +383,10 @@ mm_status mm_tune_load(mm_ctx ctx, const char* path);
  *     of a mode in one launch, the fibres staying on chip between them
  *     (products along different modes commute, so the modes' steps may be
  *     reordered; blocks of steps keep intermediate growth within 2^20 in FP32,
- *     2^200 in FP64, by the operators' norms).  0 uses one launch per product.
+ *     2^200 in FP64, by the operators' norms, and with it any decay that a later
+ *     mode's growth undoes: states within these factors of the type's largest
+ *     or smallest normal value can overflow or lose digits on the way where the
+ *     order of steps would not).  0 uses one launch per product.
  *   MM_OPT_MONITOR_EVERY (default 0 = off): mumode_expstep and
  *     gpe_strang_step record the FP64 sum |T|^2 (the discrete mass without the
  *     cell volume, §2) after every `value` steps and after the last one, on
@@ -423,7 +431,11 @@ mm_status mm_profile_begin(mm_ctx ctx);
 /* Stop recording, wait for the recorded events and return, per launch in
  * issue order, a kernel kind code (prec*1000 + complex*100 + load*10 +
  * prologue*2 + epilogue; load 0 = contiguous fibres, 1 = strided fibres,
- * 2 = generic gather) and its duration in ms.  At most max_records entries
+ * 2 = generic gather) and its duration in ms.  An expstep that runs several
+ * steps of each mode per launch on a state of at most 2 MiB with modes of at
+ * most 128 real rows is one record for the whole call (kind % 100 = 91 for a
+ * 2-D real FP64 state with both modes at most 64 long, else 90): the time
+ * between events around its launches, gaps included.  At most max_records entries
  * are written to kinds / ms (either may be NULL); *count receives the total
  * number of launches recorded. */
 mm_status mm_profile_end(mm_ctx ctx, int max_records, int* count, int* kinds, double* ms);

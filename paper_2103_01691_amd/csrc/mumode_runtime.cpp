@@ -1001,8 +1001,14 @@ mm_status mm_op_prepare_ex(mm_ctx ctx, const mm_matrix* M, mm_prec prec, unsigne
   // four steps, ratio 0.05: 4.2e-7 / 6.3e-7 / 1.5e-7; vortex n = 99, five
   // steps, 1.01: 4.6e-7 / 5.8e-7 / 3.1e-7; free Schroedinger, two steps,
   // n = 200, 1.09: 4.0e-7 / 4.2e-7 / 2.9e-7, n = 256, 1.44: 3.2e-7 / 3.9e-7 /
-  // 4.0e-7.  FP64 keeps three products there too (the same runs agree with 64
-  // bits as far as that reference reaches, 5e-15 both ways).
+  // 4.0e-7.  Those are the problems' own states; on white noise L - I rounds at
+  // its own norm whatever the state, so the error passes the block form's from
+  // a ratio of about 0.85 on (one product: 0.34 of it at 0.28, 0.7 at 0.68, 1.03
+  // to 1.3 at 1.02, 1.2 to 1.57 at 1.2), while on smooth states it stays at 0.3
+  // to 0.8 of it.  Four products are at 0.99 to 1.02 of the block form on both.
+  // FP64 keeps three products there too: against extended precision, random
+  // unitary operators of 32 to 256 rows, 1.0 to 1.08 of the block form's 2.7e-16
+  // to 7.5e-16, and half of it on L - I near the identity.
   bool res_id = false, res_c4 = false;
   if (cplx && is_res(op_layout(prec, M->rows, M->cols, cplx))) {
     bool near = false;

@@ -186,7 +186,7 @@ __device__ __forceinline__ ent res_out(const acc_t (&acc)[NP], int r) {
 
 // One tile: fibres [tile * NT, + NT), all rows, in NRB blocks of WM * MF
 // fragments of 16 rows, one after the other.
-// FORM: RF_C3, RF_RC, RF_RR.  PH: the instance carries the phases.  lds:
+// FORM: RF_C3, RF_C4, RF_RC, RF_RR.  PH: the instance carries the phases.  lds:
 // res_lds_rows(n) rows of NT + 1 entries.
 template <int PR, int FORM, int MF, int NF, bool PH>
 __device__ __forceinline__ void res_tile(const ResArgs& a, int64_t tile, void* lds) {
@@ -367,7 +367,7 @@ __device__ __forceinline__ void res_tile(const ResArgs& a, int64_t tile, void* l
 // reads run ahead of the first MFMA, and even and odd K-blocks accumulate
 // apart, so that consecutive MFMAs do not wait for each other.  us per call,
 // 20 steps: 2-D heat 64 x 64 FP64 36 (101 with the state and both operators in
-// one workgroup's LDS, 52 through res_tile), n = 64 C3 FP32 104 (125 through
+// one workgroup's LDS, 52 through res_tile), n = 64 C3 FP32 87 (108 through
 // res_tile).
 template <int PR, int FORM, int KR>
 __device__ __forceinline__ void res_run_tile(const ResArgs& a, int64_t tile, void* lds) {
