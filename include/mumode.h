@@ -380,7 +380,7 @@ mm_status mm_tune_load(mm_ctx ctx, const char* path);
 /* Context options.
  *   MM_OPT_SMALL_RUN (default 1): mumode_expstep with nsteps >= 2 and FP64 or
  *     FP32 operators of at most 256 complex / 512 real rows runs several steps
- *     of a mode in one launch, the fibres staying on chip between them
+ *     of a mode in one launch (256 at most), the fibres staying on chip between them
  *     (products along different modes commute, so the modes' steps may be
  *     reordered; blocks of steps keep intermediate growth within 2^20 in FP32,
  *     2^200 in FP64, by the operators' norms, and with it any decay that a later

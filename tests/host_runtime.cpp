@@ -386,6 +386,20 @@ void midpoint_little_memory() {
   }
 }
 
+// Steps of a mode per launch are bounded, also where nothing grows.
+void steps_per_launch() {
+  mm_ctx c = open_ctx();
+  for (int64_t n : {48, 200}) {
+    mm_op L = make_op(c, n, n, true, MM_PREC_FP64);   // norm below one
+    mm_tensor T = tensor({n, n}, MM_C128);
+    mm_op E[MM_MAXD] = {L, L};
+    const long before = rt.launches;
+    EXPECT(mumode_expstep(c, &T, E, 1000000, nullptr) == MM_OK, "%s", mm_last_error(c));
+    EXPECT(rt.launches - before >= 2 * 1000000 / 256, "%ld launches for two modes of 10^6 steps", rt.launches - before);
+  }
+  mm_destroy(c);
+}
+
 // Tune files: of the first version, entries of FP64 / FP32 products that now run
 // on the resident tiles are left out; what is written is read back whole.
 void tune_file_versions() {
@@ -422,6 +436,7 @@ int main(int argc, char** argv) {
       {"oscillator_failed_formation", oscillator_failed_formation},
       {"midpoint_little_memory", midpoint_little_memory},
       {"tune_file_versions", tune_file_versions},
+      {"steps_per_launch", steps_per_launch},
   };
   const auto it = scenarios.find(argc > 1 ? argv[1] : "");
   if (it == scenarios.end()) return 2;

@@ -29,7 +29,7 @@ def program(tmp_path_factory):
 @pytest.mark.parametrize("scenario", ["batch_failed_rebuild", "resident_plans_fit", "flat_operators",
                                       "very_many_fibres", "oscillator_little_memory",
                                       "oscillator_failed_formation", "midpoint_little_memory",
-                                      "tune_file_versions"])
+                                      "tune_file_versions", "steps_per_launch"])
 def test_host_runtime(program, scenario):
     r = subprocess.run([program, scenario], capture_output=True, text=True, timeout=300, cwd=os.path.dirname(program))
     assert r.returncode == 0, r.stdout + r.stderr
